@@ -83,13 +83,14 @@ typedef struct {
                              (non-temporal), 2 write-through (leaves no dirty L2
                              line for the release to write back) */
     int group_m;          /* tile rows per L2 swizzle group; 0 = 4 */
-    int waves_per_wg;     /* 4 or 8 wavefronts per workgroup; 0 = the tile's default
-                             (4 for 64x64, and for 256x256 in FUSED_SEQ and
-                             BULK_SYNC calls without split-K; 8 for the others).
-                             Built: 64x64 with 4; 128x128, 256x128 and 256x256
-                             with 4 or 8; 256x224 with 8 (others EUNSUPPORTED).
-                             256x256 with 4 stages 64 k at a time through
-                             registers; same results bit for bit */
+    int waves_per_wg;     /* 4 or 8 picks the build of a 256x256 tile with that many
+                             wavefronts per workgroup (4 stages 64 k at a time
+                             through registers; same results bit for bit); 0 =
+                             4 in FUSED_SEQ and BULK_SYNC calls without split-K,
+                             else 8.  The other tiles have one build of 8, run
+                             for 0 and for the values they take: 4 for 64x64,
+                             4 or 8 for 128x128 and 256x128, 8 for 256x224
+                             (others EUNSUPPORTED) */
     symtile_stream copy_stream; /* UNFUSED_PC: stream of the copy kernel; NULL = a
                              stream the heap creates on first use.  It must not
                              be the call's stream. */

@@ -12,13 +12,14 @@
 //     dispatched round-robin over the 8 XCDs, so the tiles in flight on one
 //     XCD are made spatial neighbours) followed by a GROUP_M swizzle
 //     (Section 3.4, swizzling);
-//   * main loop (Section 4, GEMM main-loop listing): 8 waves (two per SIMD;
-//     4 for 64x64 tiles), each owning a block of 32x32 MFMA accumulators
+//   * main loop (Section 4, GEMM main-loop listing): 8 waves (two per SIMD),
+//     each owning a block of 32x32 MFMA accumulators
 //     (v_mfma_f32_32x32x16_{bf16,f16}, fp32 accumulate; 16x16x32 for the
-//     256x224 tile); A and B stages of BK = 32 go through a 4-stage LDS ring,
-//     loaded 3 stages ahead, with XOR swizzles that keep both the staging
-//     writes and the fragment reads free of bank conflicts.  Both tiles go
-//     global -> LDS directly
+//     256x224 and 64x64 tiles); A and B stages go through an LDS ring (32 k
+//     each, 4 slots, for the 256-wide tiles; 64 or 128 k, see loop_cfg, for
+//     the others), loaded 2 or 3 stages ahead, with XOR swizzles that keep
+//     both the staging writes and the fragment reads free of bank conflicts.
+//     Both tiles go global -> LDS directly
 //     (buffer loads into LDS), A as [m][k] rows read with 16-byte LDS reads,
 //     B as [k][n] rows, whose MFMA operands (8 consecutive k of one column)
 //     come from two transposing LDS reads (ds_read_b64_tr_b16);
@@ -392,8 +393,8 @@ __device__ void consume_tiles(const GasParams& p, int cid, int ncons) {
 // copies the previous tile from the local slot to the w-1 other slots while
 // the compute waves run the next tile's K loop, then releases its counters
 // there.  s_barrier counts every wave of the workgroup, so the copy wave
-// takes part in exactly the compute waves' barriers: KT ring barriers and 3
-// epilogue barriers per tile, and copies a slice of the tile between them.
+// takes part in exactly the compute waves' barriers: one per stage (`stages`)
+// and 3 of the epilogue per tile, and copies a slice of the tile between them.
 // A slice must not hold the wave at a barrier waiting for memory (that would
 // stretch the compute waves' stage): row groups are loaded two intervals
 // before they are stored, into two register sets used alternately, and the
@@ -403,7 +404,7 @@ __device__ void consume_tiles(const GasParams& p, int cid, int ncons) {
 // barriers than that needs (small K) the wave stores each group as soon as
 // it is loaded.
 template <int BM, int BN, int POLICY>
-__device__ void copy_wave_tiles(const GasParams& p, int KT) {
+__device__ void copy_wave_tiles(const GasParams& p, int stages) {
     constexpr int CPR = staged_width(BN) / 8;   // 16-byte chunks per tile row
     constexpr int RPI = 64 / CPR;               // tile rows per wave-wide access
     constexpr int GROUPS = BM / RPI;
@@ -411,7 +412,7 @@ __device__ void copy_wave_tiles(const GasParams& p, int KT) {
     static_assert(64 % CPR == 0 && BM % RPI == 0 && GROUPS % 2 == 0, "copy wave split");
     const int lane = threadIdx.x & 63;
     const int G = p.gemm_wgs;
-    const int intervals = KT + 3;
+    const int intervals = stages + 3;
     const bool piped = intervals >= GROUPS + 4;
     const uint32_t group_bytes = (uint32_t)RPI * p.ldc * 2;
     int ptm = -1, ptn = -1;                     // tile waiting to be copied
@@ -512,12 +513,41 @@ __device__ void copy_wave_tiles(const GasParams& p, int KT) {
 // staged columns past BN are loaded but never read.  With NW = 8 two waves
 // share each SIMD, so one wave's MFMAs run while the other waits on LDS,
 // global loads or the barrier.
+//
+// Loop of a tile shape.  Tiles up to 256 x 128 run a deep loop: stages of 64 or 128 k (A rows as whole 128-byte lines), one
+// barrier per stage, loads two or three stages ahead.  What bounds the small
+// tiles is not the matrix cores but the fixed cost of a stage (barrier, LDS
+// latency, issue; some 270 cycles with nothing else in it) and the loads in
+// flight, so a stage carries as much k as the LDS allows, and its code has no
+// branch.  Tiles of 64 x 64 and 128 x 128 also split each stage's k between
+// two groups of four waves: a wave then holds a square block, which halves the
+// fragment reads per MFMA against eight waves side by side, and the groups'
+// sums meet once per tile through LDS.  K loop per 64 k on full chips (w = 1,
+// 32-k ring before -> now): 64 x 64 0.366 -> 0.204 us, 128 x 128 0.635 ->
+// 0.541, 256 x 128 1.011 -> 0.885; one group instead of two 0.268 (64 x 64)
+// and 0.611 (128 x 128); fragments read two steps ahead instead of one, no
+// gain.  256-wide tiles have no LDS for three 64-k stages and keep the ring.
+struct LoopCfg {
+    int kg, bk, ns;         // K groups (0: the 32-k ring), k per stage, LDS slots
+    int wgm, wgn;           // waves down and across the tile after the K loop
+};
+
+constexpr LoopCfg loop_cfg(int bm, int bn, int nw, int mf) {
+    if (bm == 64 && bn == 64) return {2, 128, 4, 4, 2};
+    if (bm == 128 && bn == 128) return {2, 64, 4, 4, 2};
+    if (bm == 256 && bn == 128) return {1, 64, 3, 4, 2};
+    const int m = mf == 32 ? 2 : 4;
+    return {0, BK, NS, m, nw / m};
+}
+
 template <int BM, int BN, bool BF16, int NW, int MF, bool CW = false, bool RED = false>
 __global__ __launch_bounds__(64 * (NW + CW))
 __attribute__((amdgpu_waves_per_eu(NW / 4 + CW, NW / 4 + CW)))
 void gas_kernel(const GasParams p) {
     constexpr int THREADS = 64 * NW;
-    constexpr int WGM = (MF == 32) ? 2 : 4, WGN = NW / WGM;   // wave grid
+    constexpr LoopCfg LC = loop_cfg(BM, BN, NW, MF);
+    constexpr bool DEEP = LC.kg > 0;
+    constexpr int WGM = LC.wgm, WGN = LC.wgn;                 // wave grid
     constexpr int WM = BM / WGM, WN = BN / WGN;               // wave tile
     constexpr int MI = WM / MF, NI = WN / MF;                 // MFMA blocks per wave
     constexpr int BNS = staged_width(BN);
@@ -525,7 +555,19 @@ void gas_kernel(const GasParams p) {
     constexpr int STAGE = A_BYTES + B_BYTES;
     constexpr int CROW = BNS * 2;                             // bytes per staged C row
     constexpr int C_BYTES = BM * CROW;
-    constexpr int LDS_BYTES = (NS * STAGE > C_BYTES) ? NS * STAGE : C_BYTES;
+    // Deep stages: A as rows of DBK k, B as DBK rows; KG groups of waves, each
+    // on its own k of every stage; a group's wave holds a block of KMI x NI.
+    constexpr int KG = DEEP ? LC.kg : 1, DBK = LC.bk;
+    constexpr int KMI = MI * KG;
+    constexpr int DA_ROW = DBK * 2, DA_BYTES = BM * DA_ROW, DB_BYTES = DBK * BNS * 2;
+    constexpr int DSTAGE = DA_BYTES + DB_BYTES;
+    constexpr int RING = DEEP ? LC.ns * DSTAGE : NS * STAGE;
+    // LDS of the K groups' exchange: behind the ring where that fits, else
+    // inside it, behind the staging of the epilogue
+    constexpr int X_BYTES = KG > 1 ? BM * BN * 4 : 0;
+    constexpr bool X_APART = RING + X_BYTES <= 150 * 1024;
+    constexpr int X_AT = X_APART ? RING : C_BYTES;
+    constexpr int LDS_BYTES = X_APART ? RING + X_BYTES : RING > C_BYTES ? RING : C_BYTES;
     constexpr int A_RPI = 1024 / kRowBytes;     // A rows per 1 KiB direct-to-LDS load
     constexpr int A_INSTR = BM / A_RPI / NW;    // direct-to-LDS A loads per wave per stage
     constexpr int ROWB = BNS * 2;               // bytes per staged B row (one k)
@@ -535,8 +577,9 @@ void gas_kernel(const GasParams p) {
     static_assert(NW == 4 || NW == 8, "4 or 8 waves");
     static_assert(MF == 32 || MF == 16, "MFMA shape");
     static_assert(MI >= 1 && NI >= 1 && WM % MF == 0 && WN % MF == 0, "unsupported tile");
-    static_assert(A_INSTR >= 1 && (BM / A_RPI) % NW == 0, "A staging split");
-    static_assert(RPI >= 1 && B_INSTR >= 1 && (BK / RPI) % NW == 0, "B staging split");
+    static_assert(DEEP || (A_INSTR >= 1 && (BM / A_RPI) % NW == 0), "A staging split");
+    static_assert(DEEP || (RPI >= 1 && B_INSTR >= 1 && (BK / RPI) % NW == 0), "B staging split");
+    static_assert(WGM * WGN == NW, "wave grid");
     using IO = TileIO<BM, BN, THREADS>;
     using acc_t = std::conditional_t<MF == 32, f32x16_t, f32x4_t>;
     constexpr int ACC_N = (MF == 32) ? 16 : 4;
@@ -548,7 +591,12 @@ void gas_kernel(const GasParams p) {
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
-    const int wm = wave / WGN, wn = wave % WGN;
+    // (K groups: waves kgrp * NW/KG .. hold the same blocks, and wave (kgrp,
+    // kwm, kwn) keeps the rows of its group's share after the K loop)
+    const int wm = KG > 1 ? (wave % (NW / KG)) / WGN * KG + wave / (NW / KG) : wave / WGN;
+    const int wn = wave % WGN;
+    // first wave of wave row `r` after the K loop (the inverse of wm)
+    [[maybe_unused]] auto wave_of = [](int r) { return r % KG * (NW / KG) + r / KG * WGN; };
     const int pid = blockIdx.x;
 
     // ---------------- consumer workgroups (Section 4.2.2) -----------------
@@ -564,8 +612,9 @@ void gas_kernel(const GasParams p) {
         // the copy wave (Section 4.2.3); the test is made visibly uniform so
         // that the compiler keeps the copy wave's addressing scalar
         if (__builtin_amdgcn_readfirstlane(wave) == NW) {
+            const int stages = DEEP ? (KT_all * BK + DBK - 1) / DBK : KT_all;
             with_store_policy(p.nontemporal, [&](auto pol) {
-                copy_wave_tiles<BM, BN, decltype(pol)::value>(p, KT_all);
+                copy_wave_tiles<BM, BN, decltype(pol)::value>(p, stages);
             });
             return;
         }
@@ -701,7 +750,9 @@ void gas_kernel(const GasParams p) {
                 acc[i][j] = mfma16<BF16>(b, a, acc[i][j]);
         };
 
-        if constexpr (V4) {
+        if constexpr (RED) {
+            // no K loop: the partials are read below
+        } else if constexpr (V4) {
             // Four waves, one per SIMD, each a 128 x 128 block of 4 x 4 MFMA
             // blocks.  A stage is 64 k: A as 256 rows of 128 bytes (whole cache
             // lines, half the L2 requests of the ring loop's 64-byte rows), B
@@ -869,6 +920,192 @@ void gas_kernel(const GasParams p) {
             }
             // (wait states between the last MFMA and reads of its result)
             asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7" ::: "memory");
+        } else if constexpr (DEEP) {
+            // The deep loop (see loop_cfg): ring of DNS slots, loads DPD stages
+            // ahead; the MFMAs of a step use the fragments read in the step
+            // before, also across the barrier.
+            constexpr int ACH = DBK / 8;               // 16-byte chunks per staged A row
+            constexpr int DA_RPI = 1024 / DA_ROW;      // A rows per 1 KiB load
+            constexpr int AU = BM / DA_RPI / NW, BU = DBK / RPI / NW, LPS = AU + BU;
+            constexpr int DNS = LC.ns, DPD = DNS - 1;  // slots, stages ahead
+            constexpr int SK = MF == 32 ? 16 : 32;     // k of one MFMA
+            constexpr int S = DBK / SK / KG;           // MFMA steps of a wave per stage
+            static_assert(AU * DA_RPI * NW == BM && BU * RPI * NW == DBK && S % 2 == 0 &&
+                          (DPD - 1) * LPS <= 63 && (NW * RPI) % 16 == 0 &&
+                          (NW * DA_RPI) % 16 == 0, "deep staging split");
+            const int kgrp = KG > 1 ? wave / (NW / KG) : 0;
+            const int kw = KG > 1 ? wave % (NW / KG) : wave;
+            const int kwm = kw / WGN, kwn = kw % WGN;
+            const int stages = (KT * BK + DBK - 1) / DBK;
+            const int kend2 = min(KT * BK, kend);      // k of the slice
+            const symtile::i32x4_t rB2 = symtile::make_rsrc_words(
+                p.B + (size_t)kbeg * p.ldb + n0,
+                kend2 > 0 ? (uint32_t)(((size_t)(kend2 - 1) * p.ldb + p.N - n0) * 2) : 0u);
+            // chunk swizzle of a staged A row: 16 consecutive rows on distinct
+            // 16-byte bank groups (128-byte rows: two rows per 256 bytes)
+            auto swz_a = [](int row) { return ACH == 8 ? (row >> 1) & 7 : row & 15; };
+            const int ar = DA_RPI * wave + lane / ACH;
+            const int ach = (lane % ACH) ^ swz_a(ar);
+            const uint32_t av = (uint32_t)(ar * p.lda * 2 + ach * 16);
+            const uint32_t au = (uint32_t)(DA_RPI * NW * p.lda * 2);
+            // (LDS addresses from a scalar wave index: the load takes its LDS base
+            // from M0, a scalar register)
+            const uint32_t lds_w = symtile::lds_addr(smem) + __builtin_amdgcn_readfirstlane(wave) * 1024;
+            // whole: every k of the stage lies inside the slice
+            auto load_stage = [&](int st, int slot, auto whole) {
+                constexpr bool WHOLE = decltype(whole)::value;
+                const int k0 = st * DBK;
+                const uint32_t dst = lds_w + slot * DSTAGE;
+                const uint32_t va =
+                    WHOLE ? av : av | ((uint32_t)(kend2 - 1 - k0 - 8 * ach) & symtile::kOOB);
+#pragma unroll
+                for (int u = 0; u < AU; ++u)
+                    symtile::buf_ld16_lds_async(rA, dst + NW * u * 1024, va, u * au + k0 * 2);
+                // (rows past the slice get kOOB itself and no scalar offset: with a
+                // wide stride their own offset could wrap around)
+#pragma unroll
+                for (int u = 0; u < BU; ++u) {
+                    const int left = kend2 - k0 - u * NW * RPI;      // rows from here to the end
+                    symtile::buf_ld16_lds_async(
+                        rB2, dst + DA_BYTES + NW * u * 1024,
+                        WHOLE || b_k_even < left ? b_v_even : symtile::kOOB,
+                        WHOLE || left > 0 ? u * b_u_bytes + (uint32_t)k0 * b_row_bytes : 0u);
+                }
+            };
+            acc_t kacc[KMI][NI];
+#pragma unroll
+            for (int i = 0; i < KMI; ++i)
+#pragma unroll
+                for (int j = 0; j < NI; ++j)
+#pragma unroll
+                    for (int e = 0; e < ACC_N; ++e) kacc[i][j][e] = 0.0f;
+            symtile::u32x4 fa[2][KMI], fb[2][NI];
+#pragma unroll
+            for (int i = 0; i < KMI; ++i) fa[1][i] = symtile::u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+            for (int j = 0; j < NI; ++j) fb[1][j] = symtile::u32x4{0u, 0u, 0u, 0u};
+            auto read_step = [&](int slot, int s, symtile::u32x4 (&a)[KMI],
+                                 symtile::u32x4 (&b)[NI]) {
+                const uint8_t* As = smem + slot * DSTAGE;
+                const uint8_t* Bs = As + DA_BYTES;
+                const int kk = kgrp * S + s;           // MFMA step within the stage
+                const int c = MF == 32 ? 2 * kk + (lane >> 5) : 4 * kk + (lane >> 4);
+#pragma unroll
+                for (int i = 0; i < KMI; ++i) {
+                    const int row = (kwm * KMI + i) * MF + a_row_lane;
+                    a[i] = *reinterpret_cast<const symtile::u32x4*>(As + row * DA_ROW +
+                                                                   ((c ^ swz_a(row)) << 4));
+                }
+#pragma unroll
+                for (int j = 0; j < NI; ++j) {
+                    const int col = kwn * WN + j * MF + tr_col;
+                    u32x2_t h[2];
+#pragma unroll
+                    for (int half = 0; half < 2; ++half) {
+                        const int k = kk * SK + tr_row + 4 * half;
+                        const uint8_t* q = Bs + k * ROWB + (((col >> 3) ^ swz_b<CPR>(k)) << 4) +
+                                           ((col & 4) << 1);
+                        h[half] = __builtin_bit_cast(
+                            u32x2_t, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                                         (__attribute__((address_space(3))) s16x4_t*)(q)));
+                    }
+                    b[j] = symtile::u32x4{h[0][0], h[0][1], h[1][0], h[1][1]};
+                }
+            };
+            auto mfma_step = [&](const symtile::u32x4 (&a)[KMI], const symtile::u32x4 (&b)[NI]) {
+#pragma unroll
+                for (int i = 0; i < KMI; ++i)
+#pragma unroll
+                    for (int j = 0; j < NI; ++j) {
+                        if constexpr (MF == 32)
+                            kacc[i][j] = mfma32<BF16>(b[j], a[i], kacc[i][j]);
+                        else
+                            kacc[i][j] = mfma16<BF16>(b[j], a[i], kacc[i][j]);
+                    }
+            };
+            constexpr int RD = KMI + 2 * NI, MM = KMI * NI;
+#pragma unroll
+            for (int d = 0; d < DPD; ++d)
+                if (d < stages) load_stage(d, d, std::false_type{});
+            int slot = 0;
+            // One stage.  steady: DPD - 1 more stages are in flight behind it and
+            // the one loaded now is whole, so the code has no branch; the last
+            // DPD + 1 stages test what is left.
+            auto run_stage = [&](int st, auto steady) {
+                constexpr bool STEADY = decltype(steady)::value;
+                const int later = stages - 1 - st;
+                if (STEADY || later >= DPD - 1)
+                    __builtin_amdgcn_s_waitcnt(vm_wait((DPD - 1) * LPS));
+                else if (DPD > 2 && later == 1)
+                    __builtin_amdgcn_s_waitcnt(vm_wait(LPS));
+                else
+                    __builtin_amdgcn_s_waitcnt(vm_wait(0));
+                wait_lds<0>();
+                ring_barrier();
+                __builtin_amdgcn_sched_barrier(0);
+                const int refill = slot == 0 ? DNS - 1 : slot - 1;   // freed by the barrier
+#pragma unroll
+                for (int s = 0; s < S; ++s) {
+                    read_step(slot, s, fa[s & 1], fb[s & 1]);
+                    mfma_step(fa[(s + 1) & 1], fb[(s + 1) & 1]);
+                    if (s == 0) {
+                        interleave_reads_mfmas<RD, MM, true>();
+                        if (STEADY || st + DPD < stages)
+                            load_stage(st + DPD, refill, std::bool_constant<STEADY>{});
+                        __builtin_amdgcn_sched_barrier(0);
+                    } else {
+                        interleave_reads_mfmas<RD, MM, false>();
+                    }
+                }
+                slot = slot == DNS - 1 ? 0 : slot + 1;
+            };
+            int st = 0;
+            for (; st + DPD < stages - 1; ++st) run_stage(st, std::true_type{});
+            for (; st < stages; ++st) run_stage(st, std::false_type{});
+            wait_lds<0>();
+            mfma_step(fa[1], fb[1]);
+            if constexpr (KG == 2) {
+                // Sum of the two groups' products: group g keeps block rows
+                // g*MI .. g*MI + MI-1 of the block both hold, and hands the
+                // others over through LDS (behind the staging of the epilogue).
+                constexpr int G4 = MI * NI * (ACC_N / 4);
+                static_assert(NW * G4 * 1024 == X_BYTES && X_AT + X_BYTES <= LDS_BYTES, "exchange");
+                uint8_t* X = smem + X_AT;
+                if constexpr (!X_APART) __syncthreads();   // every wave is done with the ring
+#pragma unroll
+                for (int i = 0; i < MI; ++i)
+#pragma unroll
+                    for (int j = 0; j < NI; ++j)
+#pragma unroll
+                        for (int g = 0; g < ACC_N / 4; ++g) {
+                            f32x4_t give;
+#pragma unroll
+                            for (int e = 0; e < 4; ++e)
+                                give[e] = kgrp ? kacc[i][j][4 * g + e] : kacc[i + MI][j][4 * g + e];
+                            *reinterpret_cast<f32x4_t*>(
+                                X + ((wave * G4 + (i * NI + j) * (ACC_N / 4) + g) * 64 + lane) * 16) = give;
+                        }
+                __syncthreads();
+                const int mate = wave ^ (NW / 2);
+#pragma unroll
+                for (int i = 0; i < MI; ++i)
+#pragma unroll
+                    for (int j = 0; j < NI; ++j)
+#pragma unroll
+                        for (int g = 0; g < ACC_N / 4; ++g) {
+                            const f32x4_t got = *reinterpret_cast<const f32x4_t*>(
+                                X + ((mate * G4 + (i * NI + j) * (ACC_N / 4) + g) * 64 + lane) * 16);
+#pragma unroll
+                            for (int e = 0; e < 4; ++e)
+                                acc[i][j][4 * g + e] =
+                                    got[e] + (kgrp ? kacc[i + MI][j][4 * g + e] : kacc[i][j][4 * g + e]);
+                        }
+            } else {
+#pragma unroll
+                for (int i = 0; i < MI; ++i)
+#pragma unroll
+                    for (int j = 0; j < NI; ++j) acc[i][j] = kacc[i][j];
+            }
         } else {
         // Pipeline over an LDS ring of NS stages of BK = 32, loads issued PD
         // stages ahead.  Each stage's fragment reads form two groups; the
@@ -1043,8 +1280,11 @@ void gas_kernel(const GasParams p) {
                 continue;
             }
             const bool last = !banded && ticketed && ticket + 1 == (uint32_t)p.split;
-            // Partial tile of slice q: each thread's accumulators, 16 bytes
-            // per (i, j, 4-value group), so a wave's access is 1 KiB contiguous.
+            // Partial tile of slice q: wave after wave, each wave's accumulators
+            // as 1 KiB (16 bytes per lane) per (i, j, 4-value group), so that an
+            // access and all of a wave's accesses together are contiguous.
+            constexpr int PART_KIB = MI * NI * (ACC_N / 4);     // of one wave
+            const uint32_t part_lane = (uint32_t)(wave * PART_KIB * 1024 + lane * 16);
             auto slot = [&](int q) {
                 return symtile::make_rsrc(p.sk_part + ((size_t)tile * p.split + q) * (BM * BN),
                                           (uint32_t)(BM * BN * 4));
@@ -1075,8 +1315,8 @@ void gas_kernel(const GasParams p) {
                                             acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
                             const symtile::u32x4 v = __builtin_bit_cast(symtile::u32x4, f);
                             symtile::buf_st16p<symtile::kStoreWriteThrough>(
-                                v, rs, (uint32_t)tid * 16,
-                                (uint32_t)(((i * NI + j) * (ACC_N / 4) + g) * THREADS * 16));
+                                v, rs, part_lane,
+                                (uint32_t)(((i * NI + j) * (ACC_N / 4) + g) * 1024));
                         }
                 }
             };
@@ -1098,8 +1338,8 @@ void gas_kernel(const GasParams p) {
                     for (int x = 0; x < BATCH; ++x) {
                         const int i = (b + x) / (NI * GPA);
                         v[x] = symtile::buf_ld16p<symtile::kLoadCoherent>(
-                            rs, covered(i, true) ? (uint32_t)tid * 16 : symtile::kOOB,
-                            (uint32_t)((b + x) * THREADS * 16));
+                            rs, covered(i, true) ? part_lane : symtile::kOOB,
+                            (uint32_t)((b + x) * 1024));
                     }
 #pragma unroll
                     for (int x = 0; x < BATCH; ++x) {
@@ -1118,8 +1358,8 @@ void gas_kernel(const GasParams p) {
                 // rounded straight into the LDS staging of the epilogue (the
                 // first kernel's partials were completed by the kernel
                 // boundary).  Every wave shares the band: chunk x is 16 bytes
-                // of a partial (4 consecutive columns of one row), taken in
-                // memory order, so a wave reads 1 KiB runs; CH chunks of QB
+                // of a partial (4 consecutive columns of one row), taken so that
+                // a wave reads 1 KiB runs; CH chunks of QB
                 // slices are in flight per thread at once.
                 constexpr int GPA = ACC_N / 4;
                 constexpr int PER_BR = NI * GPA * WGN * 64;    // chunks per block row
@@ -1142,8 +1382,8 @@ void gas_kernel(const GasParams p) {
                             const int br = br0 + x / PER_BR, rem = x % PER_BR;
                             const int jg = rem / (WGN * 64), wl = rem % (WGN * 64);
                             const uint32_t off =
-                                (uint32_t)(((((br % MI) * NI + jg / GPA) * GPA + jg % GPA) * THREADS +
-                                            ((br / MI) * WGN + wl / 64) * 64 + wl % 64) * 16);
+                                (uint32_t)((((wave_of(br / MI) + wl / 64) * PART_KIB +
+                                             (br % MI) * NI * GPA + jg) * 64 + wl % 64) * 16);
 #pragma unroll
                             for (int qq = 0; qq < QB; ++qq) {
                                 const int q = min(q0 + qq, p.split - 1);
@@ -1303,14 +1543,17 @@ void gas_kernel(const GasParams p) {
         const symtile::TileGeom geom = out_tile<BM, BN, THREADS>(p, tm, tn);
         const symtile::TileLanes lanes = symtile::tile_lanes(geom, tid, THREADS);
         const int c = tid % IO::CPR, r0 = tid / IO::CPR;
-        const uint32_t voff = lanes.voff;
+        // a band may be a part of one pass: the threads of its other rows idle
+        const bool idle_row =
+            banded && band_rows < IO::RP && r0 / band_rows != ks % max(IO::RP / band_rows, 1);
+        const uint32_t voff = idle_row ? symtile::kOOB : lanes.voff;
         const uint32_t pass_bytes = lanes.pass_bytes;
         const uint8_t* crow = Cs + r0 * CROW + ((c ^ (r0 & 7)) << 4);
         // passes [pass_lo, pass_hi) hold the rows to store: the whole tile,
         // or this slice's band (the host checks that a band is a whole
         // number of passes)
-        const int pass_lo = banded ? ks * (band_rows / IO::RP) : 0;
-        const int pass_hi = banded ? pass_lo + band_rows / IO::RP : IO::PASSES;
+        const int pass_lo = banded ? ks * band_rows / IO::RP : 0;
+        const int pass_hi = banded ? pass_lo + max(band_rows / IO::RP, 1) : IO::PASSES;
 #pragma unroll 1
         for (int b = pass_lo; b < pass_hi; b += IO::U) {
             symtile::u32x4 v[IO::U];
@@ -1428,7 +1671,8 @@ __global__ __launch_bounds__(copy_threads<BM>()) void consumer_kernel(const GasP
 struct Variant {
     int bm, bn;
     bool bf16;
-    int waves;
+    int waves;                   // of the build
+    int asked;                   // wave counts that select it, as a sum of 4 and 8
     const void* gas;
     const void* scatter;
     const void* consumer;
@@ -1439,11 +1683,11 @@ struct Variant {
 };
 
 // Rows of a banded split-K reduction band must cover whole MFMA accumulator
-// blocks (MF rows) and whole passes of the epilogue's row stores.
-template <int BM, int BN, int NW, int MF>
+// blocks (MF rows); the quantum is 32 rows, 16 for the 256 x 224 tile.
+template <int BM, int BN, int MF>
 constexpr int band_quantum() {
-    constexpr int rp = TileIO<BM, BN, 64 * NW>::RP;
-    return rp > MF ? rp : MF;
+    static_assert(32 % MF == 0, "a band is whole accumulator blocks");
+    return BN == 224 ? 16 : 32;
 }
 
 // The copy-wave kernel is instantiated only for the shapes that use it.
@@ -1455,31 +1699,30 @@ const void* wave_spec_kernel() {
         return nullptr;
 }
 
-template <int BM, int BN, bool BF16, int NW, int MF = 32, bool WS = false>
+template <int BM, int BN, bool BF16, int NW, int MF = 32, int ASKED = NW, bool WS = false>
 Variant make_variant() {
-    return Variant{BM, BN, BF16, NW,
+    return Variant{BM, BN, BF16, NW, ASKED,
                    reinterpret_cast<const void*>(&gas_kernel<BM, BN, BF16, NW, MF>),
                    reinterpret_cast<const void*>(&scatter_kernel<BM, BN>),
                    reinterpret_cast<const void*>(&consumer_kernel<BM, BN>),
                    copy_threads<BM>(), wave_spec_kernel<BM, BN, BF16, NW, MF, WS>(),
                    reinterpret_cast<const void*>(&gas_kernel<BM, BN, BF16, NW, MF, false, true>),
-                   band_quantum<BM, BN, NW, MF>()};
+                   band_quantum<BM, BN, MF>()};
 }
 
 // waves == 0 picks the first entry of the shape (the default wave count).
 const Variant* find_variant(int bm, int bn, bool bf16, int waves) {
     static const Variant table[] = {
-        make_variant<64, 64, false, 4>(),    make_variant<64, 64, true, 4>(),
-        make_variant<128, 128, false, 8>(),  make_variant<128, 128, true, 8>(),
-        make_variant<128, 128, false, 4>(),  make_variant<128, 128, true, 4>(),
-        make_variant<256, 128, false, 8, 32, true>(), make_variant<256, 128, true, 8, 32, true>(),
-        make_variant<256, 128, false, 4>(),  make_variant<256, 128, true, 4>(),
+        make_variant<64, 64, false, 8, 16, 4>(), make_variant<64, 64, true, 8, 16, 4>(),
+        make_variant<128, 128, false, 8, 32, 4 + 8>(), make_variant<128, 128, true, 8, 32, 4 + 8>(),
+        make_variant<256, 128, false, 8, 32, 4 + 8, true>(),
+        make_variant<256, 128, true, 8, 32, 4 + 8, true>(),
         make_variant<256, 256, false, 8>(),  make_variant<256, 256, true, 8>(),
         make_variant<256, 256, false, 4>(),  make_variant<256, 256, true, 4>(),
         make_variant<256, 224, false, 8, 16>(), make_variant<256, 224, true, 8, 16>(),
     };
     for (const Variant& v : table)
-        if (v.bm == bm && v.bn == bn && v.bf16 == bf16 && (waves == 0 || v.waves == waves))
+        if (v.bm == bm && v.bn == bn && v.bf16 == bf16 && (waves == 0 || (v.asked & waves)))
             return &v;
     return nullptr;
 }
@@ -1493,7 +1736,13 @@ const Variant* find_wave_spec_variant(int bm, int bn, bool bf16) {
     return nullptr;
 }
 
-symtile_status coresident_limit(const Variant* v, int device, int* cus, int* limit) {
+// *resident: workgroups of the kernel that can be resident at once.  *limit:
+// the largest grid a schedule with waiting workgroups accepts.  They differ
+// for 64 x 64 tiles, whose deep LDS ring leaves room for one workgroup per CU
+// where its 32 KiB predecessor left room for four: larger grids are accepted
+// as before and run as a resident grid that takes more tiles per workgroup.
+symtile_status coresident_limit(const Variant* v, int device, int* cus, int* limit,
+                                int* resident) {
     int n_cu = symtile_host::cu_count(device);
     if (n_cu <= 0) return symtile_host::fail(SYMTILE_EHIP, "cannot read the CU count");
     // workgroups of a kernel per CU: fixed for the process, so asked once per
@@ -1512,7 +1761,8 @@ symtile_status coresident_limit(const Variant* v, int device, int* cus, int* lim
         per_cu_known[{v->gas, device}] = per_cu;
     }
     *cus = n_cu;
-    *limit = per_cu * n_cu;
+    *resident = per_cu * n_cu;
+    *limit = (v->bm == 64 ? std::max(per_cu, 4) : per_cu) * n_cu;
     return SYMTILE_OK;
 }
 
@@ -1582,8 +1832,8 @@ extern "C" symtile_status symtile_device_info(int device, int tile_m, int tile_n
     if (tile_m == 0 && tile_n == 0) tile_m = tile_n = 256;
     const Variant* v = find_variant(tile_m, tile_n, true, 0);
     if (!v) return symtile_host::fail(SYMTILE_EUNSUPPORTED, "tile shape not built");
-    int cus = 0, lim = 0;
-    if (symtile_status st = coresident_limit(v, device, &cus, &lim)) return st;
+    int cus = 0, lim = 0, resident = 0;
+    if (symtile_status st = coresident_limit(v, device, &cus, &lim, &resident)) return st;
     if (cu_count) *cu_count = cus;
     if (max_coresident_wgs) *max_coresident_wgs = lim;
     return SYMTILE_OK;
@@ -1688,8 +1938,8 @@ extern "C" symtile_status symtile_gemm_all_scatter(
         }
     }
 
-    int cus = 0, limit = 0;
-    if (symtile_status st = coresident_limit(v, h->device, &cus, &limit)) return st;
+    int cus = 0, limit = 0, resident = 0;
+    if (symtile_status st = coresident_limit(v, h->device, &cus, &limit, &resident)) return st;
 
     GasParams p;
     p.A = static_cast<const uint16_t*>(A);
@@ -1761,10 +2011,13 @@ extern "C" symtile_status symtile_gemm_all_scatter(
             // the reduction kernel, which spreads the sum and the stores over
             // every CU instead of one slice per tile (banded: every slice
             // then pays a partial write, a wait and a second ticket)
+            // (a banded call whose workgroups are not all resident takes the
+            // reduction kernel too: the same sums, and nothing waits)
             const bool automatic = cfg.split_reduce == SYMTILE_SPLIT_REDUCE_AUTO;
             p.sk_band = cfg.split_reduce == SYMTILE_SPLIT_REDUCE_BANDED ||
                         (automatic && fits && split == 2);
-            if (cfg.split_reduce == SYMTILE_SPLIT_REDUCE_KERNEL || (automatic && split > 2))
+            if (cfg.split_reduce == SYMTILE_SPLIT_REDUCE_KERNEL || (automatic && split > 2) ||
+                (p.sk_band == 1 && g > resident))
                 p.sk_band = 2;
         }
         p.role = cfg.variant == SYMTILE_FUSED_SEQ ? ROLE_FUSED : ROLE_LOCAL_ONLY;
@@ -1855,6 +2108,10 @@ extern "C" symtile_status symtile_gemm_all_scatter(
         return fail(SYMTILE_EUNSUPPORTED,
                     "gemm_wgs + copy_wgs = " + std::to_string(g + c) +
                         " exceeds the co-resident limit " + std::to_string(limit));
+    if (g + c > resident) {                      // the same split of a resident grid
+        c = std::max(1, (int)((int64_t)c * resident / (g + c)));
+        g = resident - c;
+    }
     if (world_size == 1) c = std::min(c, ntiles);
     p.gemm_wgs = g;
     p.copy_wgs = c;

@@ -926,3 +926,50 @@ def test_random_calls_match_oracle(case):
     check_gathered(p, want)
     if split > 1:
         assert np.all(_ws_counters(p) == 0)
+
+
+# ---------------------------------------------------------------- deep-stage loops
+
+@pytest.mark.parametrize("K", [8, 56, 64, 72, 120, 128, 136, 248, 384, 392, 520])
+@pytest.mark.parametrize("tile", [(64, 64), (128, 128), (256, 128)], ids="%dx%d".__mod__)
+def test_deep_stage_edges_match_oracle(tile, K):
+    """K around the 64-k and 128-k stages (one stage, a stage cut short, one
+    more than the ring holds), in one slice and in slices that end inside a
+    stage; the rows and columns are ragged too.  Each element within the fp32
+    accumulation bound; every split-K reduction leaves the same bits."""
+    world, M, N = 2, tile[0] + 9, tile[1] + 24
+    p = Problem(world, M, N, K, "bf16", *tile, seed=K)
+    want = {1: oracle_block_bounded(p.A, p.shards[1], "bf16")}
+    stages = -(-K // 32)
+    for split in sorted({1, min(2, stages), min(3, stages)}):
+        heaps = []
+        for mode in (0,) if split == 1 else (1, 2, 3):
+            if mode == 2 and (tile[0] % split or tile[0] // split % 32):
+                continue
+            p.sentinel()
+            p.run(1, FUSED, split_k=split, split_reduce=mode)
+            p.barrier()
+            check_gathered(p, want)
+            heaps.append(u16(p.out.C_all()).copy())
+        assert all(np.array_equal(h, heaps[0]) for h in heaps)
+
+
+def test_wg_spec_64x64_grid_larger_than_resident():
+    """64 x 64 tiles take up to four workgroups per CU in a WG_SPEC call; the
+    grid that runs holds one per CU.  Results as from a fused call."""
+    p = Problem(2, 1300, 1288, 136, "f16", 64, 64, seed=3)
+    cus, limit = sym().symtile_device_info(0, 64, 64)
+    assert limit >= 4 * cus
+    p.sentinel()
+    p.run(0, FUSED)
+    p.barrier()
+    ref = u16(p.out.C_all()).copy()
+    for copy_wgs in (1, limit // 4, limit - 1):
+        p.sentinel()
+        p.run(0, WGSPEC, gemm_wgs=limit - copy_wgs, copy_wgs=copy_wgs)
+        p.barrier()
+        assert np.array_equal(u16(p.out.C_all()), ref), copy_wgs
+    with pytest.raises(sym().SymtileError) as e:
+        p.run(0, WGSPEC, gemm_wgs=limit, copy_wgs=1)
+    assert e.value.name == "EUNSUPPORTED"
+    p.heap.barrier()
