@@ -102,6 +102,10 @@ struct GasParams {
     // slice to arrive sums and stores the whole tile; 2 = every slice only
     // writes its partial (the first kernel of the reduction-kernel mode).
     int sk_band;
+    // WG_SPEC and UNFUSED_PC: how many of the world - 1 other slots a producer
+    // stores itself, of its last tile and of the tiles before it; the
+    // consumers put the others.
+    int direct_last, direct_mid;
     // ROLE_REDUCE: bands of rows per tile (units = tiles * reduce_bands), and
     // whether the tile goes to every slot (fused) or the local one (bulk).
     int reduce_bands, reduce_all;
@@ -330,21 +334,24 @@ __device__ __forceinline__ uint16_t* out_tile_ptr(const GasParams& p, int BM, in
     return p.C + (size_t)p.rank * p.N + (size_t)tm * BM * p.ldc + (size_t)tn * BN;
 }
 
-// Copy one finished tile from the local heap to every other heap (the put of
-// Sections 4.1.1 and 4.2.2) and release its counters there.  LOAD is the
+// Copy one finished tile from the local heap to the heaps of ranks rank + d,
+// d in [d0, world) (the put of Sections 4.1.1 and 4.2.2), and release its
+// counters there, by THREADS threads (a workgroup or one wave).  LOAD is the
 // policy of the tile's loads (coherent after a flag_wait_coherent).
 template <int BM, int BN, int THREADS, int POLICY, int LOAD = symtile::kLoadDefault>
-__device__ void put_tile_to_peers(const GasParams& p, int tm, int tn) {
+__device__ void put_tile_to_peers(const GasParams& p, int tm, int tn, int tid, int d0) {
     using IO = TileIO<BM, BN, THREADS>;
-    const int tid = threadIdx.x;
     symtile::put_ranks<POLICY, IO::U, LOAD>(out_tile_ptr(p, BM, BN, tm, tn),
-                                            out_tile<BM, BN, THREADS>(p, tm, tn), p.rank, 1,
+                                            out_tile<BM, BN, THREADS>(p, tm, tn), p.rank, d0,
                                             p.world, p.world, p.bases, tid, THREADS);
-    symtile::wg_stores_done();
-    if (tid < 64) {            // wave 0: one release, then lane d counts slot rank + d
+    if constexpr (THREADS > 64)
+        symtile::wg_stores_done();
+    else
+        __builtin_amdgcn_s_waitcnt(vm_wait(0));
+    if (tid < 64) {            // one wave: one release, then lane d counts slot rank + d
         release_output<POLICY>();
         uint32_t* flag = p.arrived + ((size_t)p.rank * p.tiles_m + tm) * p.tiles_n + tn;
-        const int d = tid + 1;
+        const int d = tid + d0;
         if (d < p.world)
             symtile::flag_signal(symtile::translate(flag, p.rank, (p.rank + d) % p.world, p.bases));
     }
@@ -353,35 +360,58 @@ __device__ void put_tile_to_peers(const GasParams& p, int tm, int tn) {
 // Consumer loop of the producer-consumer schedules (Sections 4.1.2 and
 // 4.2.2): consumer `cid` of `ncons` takes tiles cid, cid + ncons, ... in the
 // producers' tile order, waits (bounded) until the producer's ready counter
-// reaches the epoch, acquires, and puts the tile to the other heaps.  A
+// reaches the epoch, acquires, and puts the tile to the heaps its producer
+// leaves to the consumers.  A
 // timed-out wait records ERR_TIMEOUT and ends this consumer.  With the
 // write-through output policy the producers' tiles are read back with
 // coherent loads, so the acquire needs no L2 invalidate.
+//
+// A tile costs a consumer some 4 us of waiting whatever its size (the poll,
+// its loads, the acknowledgement of its stores), so tiles of up to 32 KiB are
+// taken by single waves, each a consumer of its own: as many tiles are in
+// flight per workgroup as it has waves.  (fp16 8192x512x1024, w = 8, 64x64
+// tiles, 32 consumer workgroups: 238 -> 92 us a call together with the slots
+// that the producers store themselves, see share_slots.)
 template <int BM, int BN, int THREADS>
 __device__ void consume_tiles(const GasParams& p, int cid, int ncons) {
+    constexpr bool PER_WAVE = BM * BN * 2 <= 32768;
+    constexpr int MOVERS = PER_WAVE ? 64 : THREADS;       // threads that move one tile
     __shared__ int s_ok;
-    const int tid = threadIdx.x;
+    const int tid = PER_WAVE ? threadIdx.x & 63 : threadIdx.x;
+    if constexpr (PER_WAVE) {
+        // (consecutive tiles go to different workgroups)
+        cid += __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * ncons;
+        ncons *= THREADS / 64;
+    }
     for (int t = cid; t < p.num_tiles; t += ncons) {
         int tm, tn;
         tile_coords(t, p.gemm_wgs, p, tm, tn);
         uint64_t* tr = tile_trace(p, tm, tn);
+        int ok = 0;
         if (tid == 0) {
             if (tr) tr[SYMTILE_TRACE_COPY_WAIT] = symtile::clock_now();
             const uint32_t* rdy = p.ready + tm * p.tiles_n + tn;
-            const bool ok = p.nontemporal == 2
-                                ? symtile::flag_wait_coherent(rdy, p.epoch, p.spin_limit)
-                                : symtile::flag_wait(rdy, p.epoch, p.spin_limit);
+            ok = p.nontemporal == 2 ? symtile::flag_wait_coherent(rdy, p.epoch, p.spin_limit)
+                                    : symtile::flag_wait(rdy, p.epoch, p.spin_limit);
             if (!ok) symtile::raise_error(p.err, symtile::ERR_TIMEOUT);
             if (tr) tr[SYMTILE_TRACE_COPY_GO] = symtile::clock_now();
-            s_ok = ok;
+            if (!PER_WAVE) s_ok = ok;
         }
-        __syncthreads();
-        if (!s_ok) return;
+        if constexpr (PER_WAVE) {
+            ok = __builtin_amdgcn_readfirstlane(ok);
+            asm volatile("" ::: "memory");      // no load moves up past the wait
+        } else {
+            __syncthreads();
+            ok = s_ok;
+        }
+        if (!ok) return;
         with_store_policy(p.nontemporal, [&](auto pol) {
             constexpr int P = decltype(pol)::value;
-            put_tile_to_peers<BM, BN, THREADS, P,
+            put_tile_to_peers<BM, BN, MOVERS, P,
                               P == symtile::kStoreWriteThrough ? symtile::kLoadCoherent
-                                                               : symtile::kLoadDefault>(p, tm, tn);
+                                                               : symtile::kLoadDefault>(
+                p, tm, tn, tid,
+                1 + (t + p.gemm_wgs >= p.num_tiles ? p.direct_last : p.direct_mid));
         });
         if (tr && tid == 0) tr[SYMTILE_TRACE_COPY_DONE] = symtile::clock_now();
     }
@@ -1554,87 +1584,102 @@ void gas_kernel(const GasParams p) {
         // number of passes)
         const int pass_lo = banded ? ks * band_rows / IO::RP : 0;
         const int pass_hi = banded ? pass_lo + max(band_rows / IO::RP, 1) : IO::PASSES;
+        // Destinations [d_lo, d_hi), counted from this rank's own slot.  A
+        // producer of the producer-consumer schedules stores its own slot and
+        // signals the consumers, then stores its share of the others (see
+        // direct_last) while they put the rest.
+        int d_lo = 0, d_hi = n_dst;
+        for (;;) {
 #pragma unroll 1
-        for (int b = pass_lo; b < pass_hi; b += IO::U) {
-            symtile::u32x4 v[IO::U];
+            for (int b = pass_lo; b < pass_hi; b += IO::U) {
+                symtile::u32x4 v[IO::U];
 #pragma unroll
-            for (int u = 0; u < IO::U; ++u)
-                v[u] = *reinterpret_cast<const symtile::u32x4*>(
-                    crow + min(b + u, IO::PASSES - 1) * IO::RP * CROW);
-            for (int d = 0; d < n_dst; ++d) {
-                const symtile::rsrc_t rd =
-                    symtile::tile_rsrc(tile_local, geom, p.rank, (p.rank + d) % p.world, p.bases);
-                with_store_policy(p.nontemporal, [&](auto pol) {
+                for (int u = 0; u < IO::U; ++u)
+                    v[u] = *reinterpret_cast<const symtile::u32x4*>(
+                        crow + min(b + u, IO::PASSES - 1) * IO::RP * CROW);
+                for (int d = d_lo; d < d_hi; ++d) {
+                    const symtile::rsrc_t rd =
+                        symtile::tile_rsrc(tile_local, geom, p.rank, (p.rank + d) % p.world, p.bases);
+                    with_store_policy(p.nontemporal, [&](auto pol) {
 #pragma unroll
-                    for (int u = 0; u < IO::U; ++u)
-                        if (b + u < pass_hi)       // uniform: a band may be one pass
-                            symtile::buf_st16p<decltype(pol)::value>(v[u], rd, voff,
-                                                                     (b + u) * pass_bytes);
-                });
+                        for (int u = 0; u < IO::U; ++u)
+                            if (b + u < pass_hi)       // uniform: a band may be one pass
+                                symtile::buf_st16p<decltype(pol)::value>(v[u], rd, voff,
+                                                                         (b + u) * pass_bytes);
+                    });
+                }
             }
-        }
-        symtile::wg_stores_done();     // also orders the LDS reads above before reuse
-        if (tid < 64) {                // wave 0: one release, then lane d counts slot rank + d
-            bool publish = true;
-            if (reducer) {
-                // Reduction kernel: the tile is whole once every band is
-                // stored; each band releases its stores and takes a ticket,
-                // and the one that draws the last resets the counter and
-                // publishes the tile's counters.  This mode leaves counter 1
-                // alone, so a non-zero counter 1 (read above) or a ticket
-                // past the band count means the workspace was not zero when
-                // the call started: the data stored is this call's, but the
-                // tile is not published, and the error is reported.
-                release_output(p.nontemporal);
-                uint32_t* cnt = p.sk_cnt + 2 * (tm * p.tiles_n + tn);
-                uint32_t u = 0;
-                if (tid == 0) {
-                    u = symtile::atomic_add<__ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT>(cnt, 1u);
-                    if (red_cnt1 != 0 || u >= (uint32_t)p.reduce_bands)
-                        symtile::raise_error(p.err, symtile::ERR_WORKSPACE);
-                }
-                u = __shfl(u, 0);
-                const uint32_t w1 = __shfl(red_cnt1, 0);
-                publish = w1 == 0 && u == (uint32_t)p.reduce_bands - 1u;
-                if (publish) {
-                    if (p.nontemporal != 2) symtile::fence_acquire<__HIP_MEMORY_SCOPE_AGENT>();
-                    if (tid == 0)
-                        symtile::atomic_xchg<__ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT>(cnt, 0u);
-                }
-            } else if (banded) {
-                // Banded: the tile is whole once every slice has stored its
-                // band.  Each slice releases its stores and takes a second
-                // ticket on counter 0 (the first round of tickets left it at
-                // split); the one that draws 2*split - 1 acquires the others'
-                // stores, resets the counters for the next call and publishes
-                // the tile's counters behind a release of its own.
-                release_output(p.nontemporal);
-                uint32_t* cnt = p.sk_cnt + 2 * (tm * p.tiles_n + tn);
-                uint32_t u2 = 0;
-                if (tid == 0)
-                    u2 = symtile::atomic_add<__ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT>(cnt, 1u);
-                u2 = __shfl(u2, 0);
-                publish = u2 == 2u * (uint32_t)p.split - 1u;
-                if (publish) {
-                    // the other slices' band stores happen before the counters
-                    // move: written through, they were in memory before their
-                    // slices' tickets; otherwise acquire their releases
-                    if (p.nontemporal != 2) symtile::fence_acquire<__HIP_MEMORY_SCOPE_AGENT>();
+            symtile::wg_stores_done();     // also orders the LDS reads above before reuse
+            if (tid < 64) {                // wave 0: one release, then lane d counts slot rank + d
+                bool publish = true;
+                if (reducer) {
+                    // Reduction kernel: the tile is whole once every band is
+                    // stored; each band releases its stores and takes a ticket,
+                    // and the one that draws the last resets the counter and
+                    // publishes the tile's counters.  This mode leaves counter 1
+                    // alone, so a non-zero counter 1 (read above) or a ticket
+                    // past the band count means the workspace was not zero when
+                    // the call started: the data stored is this call's, but the
+                    // tile is not published, and the error is reported.
+                    release_output(p.nontemporal);
+                    uint32_t* cnt = p.sk_cnt + 2 * (tm * p.tiles_n + tn);
+                    uint32_t u = 0;
                     if (tid == 0) {
-                        symtile::atomic_xchg<__ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT>(cnt, 0u);
-                        symtile::atomic_xchg<__ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT>(cnt + 1, 0u);
+                        u = symtile::atomic_add<__ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT>(cnt, 1u);
+                        if (red_cnt1 != 0 || u >= (uint32_t)p.reduce_bands)
+                            symtile::raise_error(p.err, symtile::ERR_WORKSPACE);
+                    }
+                    u = __shfl(u, 0);
+                    const uint32_t w1 = __shfl(red_cnt1, 0);
+                    publish = w1 == 0 && u == (uint32_t)p.reduce_bands - 1u;
+                    if (publish) {
+                        if (p.nontemporal != 2) symtile::fence_acquire<__HIP_MEMORY_SCOPE_AGENT>();
+                        if (tid == 0)
+                            symtile::atomic_xchg<__ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT>(cnt, 0u);
+                    }
+                } else if (banded) {
+                    // Banded: the tile is whole once every slice has stored its
+                    // band.  Each slice releases its stores and takes a second
+                    // ticket on counter 0 (the first round of tickets left it at
+                    // split); the one that draws 2*split - 1 acquires the others'
+                    // stores, resets the counters for the next call and publishes
+                    // the tile's counters behind a release of its own.
+                    release_output(p.nontemporal);
+                    uint32_t* cnt = p.sk_cnt + 2 * (tm * p.tiles_n + tn);
+                    uint32_t u2 = 0;
+                    if (tid == 0)
+                        u2 = symtile::atomic_add<__ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT>(cnt, 1u);
+                    u2 = __shfl(u2, 0);
+                    publish = u2 == 2u * (uint32_t)p.split - 1u;
+                    if (publish) {
+                        // the other slices' band stores happen before the counters
+                        // move: written through, they were in memory before their
+                        // slices' tickets; otherwise acquire their releases
+                        if (p.nontemporal != 2) symtile::fence_acquire<__HIP_MEMORY_SCOPE_AGENT>();
+                        if (tid == 0) {
+                            symtile::atomic_xchg<__ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT>(cnt, 0u);
+                            symtile::atomic_xchg<__ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT>(cnt + 1, 0u);
+                        }
                     }
                 }
+                if (publish) {
+                    if (p.trace && tid == 0 && d_lo == 0)
+                        tile_trace(p, tm, tn)[SYMTILE_TRACE_STORED] = symtile::clock_now();
+                    release_output(p.nontemporal);
+                    uint32_t* flag = p.arrived + ((size_t)p.rank * p.tiles_m + tm) * p.tiles_n + tn;
+                    if (tid >= d_lo && tid < d_hi)
+                        symtile::flag_signal(symtile::translate(flag, p.rank, (p.rank + tid) % p.world, p.bases));
+                    if (tid == 0 && p.role == ROLE_WG_SPEC && d_lo == 0)
+                        symtile::flag_signal(p.ready + tm * p.tiles_n + tn);
+                    if (p.trace && tid == 0) tile_trace(p, tm, tn)[SYMTILE_TRACE_RELEASED] = symtile::clock_now();
+                }
             }
-            if (publish) {
-                if (p.trace && tid == 0) tile_trace(p, tm, tn)[SYMTILE_TRACE_STORED] = symtile::clock_now();
-                release_output(p.nontemporal);
-                uint32_t* flag = p.arrived + ((size_t)p.rank * p.tiles_m + tm) * p.tiles_n + tn;
-                if (tid < n_dst)
-                    symtile::flag_signal(symtile::translate(flag, p.rank, (p.rank + tid) % p.world, p.bases));
-                if (tid == 0 && p.role == ROLE_WG_SPEC) symtile::flag_signal(p.ready + tm * p.tiles_n + tn);
-                if (p.trace && tid == 0) tile_trace(p, tm, tn)[SYMTILE_TRACE_RELEASED] = symtile::clock_now();
-            }
+            const int direct = p.role != ROLE_WG_SPEC || d_lo > 0 ? 0
+                               : t + G >= p.num_tiles             ? p.direct_last
+                                                                  : p.direct_mid;
+            if (direct == 0) break;
+            d_lo = 1;
+            d_hi = 1 + direct;
         }
     }
 }
@@ -1654,7 +1699,8 @@ __global__ __launch_bounds__(copy_threads<BM>()) void scatter_kernel(const GasPa
         if (tr && threadIdx.x == 0)
             tr[SYMTILE_TRACE_COPY_WAIT] = tr[SYMTILE_TRACE_COPY_GO] = symtile::clock_now();
         with_store_policy(p.nontemporal, [&](auto pol) {
-            put_tile_to_peers<BM, BN, copy_threads<BM>(), decltype(pol)::value>(p, tm, tn);
+            put_tile_to_peers<BM, BN, copy_threads<BM>(), decltype(pol)::value>(p, tm, tn,
+                                                                                threadIdx.x, 1);
         });
         if (tr && threadIdx.x == 0) tr[SYMTILE_TRACE_COPY_DONE] = symtile::clock_now();
     }
@@ -1764,6 +1810,32 @@ symtile_status coresident_limit(const Variant* v, int device, int* cus, int* lim
     *resident = per_cu * n_cu;
     *limit = (v->bm == 64 ? std::max(per_cu, 4) : per_cu) * n_cu;
     return SYMTILE_OK;
+}
+
+// Producer-consumer schedules: the slots a producer stores itself
+// (GasParams::direct_last, direct_mid).
+//
+// Last tiles.  All producers finish their last tile at about the same time
+// and then have nothing to do, while a consumer workgroup moves some 50 GB/s:
+// left to the consumers, the last tiles are a tail that only c of the g + c
+// workgroups work on (bf16 4096x8192x3584, w = 8: 313 us with 224 + 32
+// workgroups and 729 with 248 + 8, against 230 for the fused call).  So each
+// takes the share of the slots that its workgroups are of the grid, the
+// consumers at least one.
+// Tiles before the last.  The consumers take what they can move during one
+// tile's K loop, at 50 GB/s per workgroup and 4.5 TFLOP/s per producer (what
+// both reach on the large shapes), and at least one slot; the producers
+// store the rest, which would only queue up behind the consumers.
+void share_slots(GasParams& p, int bm, int bn, int g, int c) {
+    const int others = p.world - 1;
+    p.direct_last = p.direct_mid = 0;
+    if (others <= 1) return;
+    const int producers = std::min(g, p.num_tiles);
+    const int last = (int)(others * (double)c / (producers + c) + 0.5);
+    p.direct_last = others - std::min(std::max(last, 1), others);
+    const double loop_s = 2.0 * bm * bn * (double)p.K / 4.5e12;
+    const double slots = c * 50e9 * loop_s / ((double)producers * bm * bn * 2);
+    p.direct_mid = others - (int)std::min(std::max(slots, 1.0), (double)others);
 }
 
 // Split-K workspace: two counters per tile, rounded up to 256 bytes, then
@@ -1987,6 +2059,7 @@ extern "C" symtile_status symtile_gemm_all_scatter(
 
     const int ntiles = (int)num_tiles;
     p.sk_band = 0;
+    p.direct_last = p.direct_mid = 0;
     p.reduce_bands = 1;
     p.reduce_all = 0;
     if (cfg.variant == SYMTILE_FUSED_SEQ || cfg.variant == SYMTILE_BULK_SYNC) {
@@ -2044,7 +2117,9 @@ extern "C" symtile_status symtile_gemm_all_scatter(
                                         stream));
         }
         if (cfg.variant == SYMTILE_BULK_SYNC && world_size > 1) {
-            int c = cfg.copy_wgs > 0 ? cfg.copy_wgs : cus;
+            // 16 waves a CU (a tile is a round trip to memory and back for its
+            // workgroup, so as many tiles as fit are in flight at once)
+            int c = cfg.copy_wgs > 0 ? cfg.copy_wgs : cus * (1024 / v->copy_threads);
             c = std::min(c, ntiles);
             p.copy_wgs = c;
             SYMTILE_HIP(hipLaunchKernel(v->scatter, dim3(c), dim3(v->copy_threads), args, 0, stream));
@@ -2089,6 +2164,7 @@ extern "C" symtile_status symtile_gemm_all_scatter(
         p.gemm_wgs = g;
         p.copy_wgs = std::min(c, ntiles);
         p.role = ROLE_WG_SPEC;
+        share_slots(p, cfg.tile_m, cfg.tile_n, g, p.copy_wgs);
         void* args[] = {&p};
         SYMTILE_HIP(hipEventRecord(h->ev_fork, stream));
         SYMTILE_HIP(hipStreamWaitEvent(cs, h->ev_fork, 0));
@@ -2116,6 +2192,7 @@ extern "C" symtile_status symtile_gemm_all_scatter(
     p.gemm_wgs = g;
     p.copy_wgs = c;
     p.role = ROLE_WG_SPEC;
+    share_slots(p, cfg.tile_m, cfg.tile_n, g, std::min(c, ntiles));
     void* args[] = {&p};
     SYMTILE_HIP(hipLaunchKernel(v->gas, dim3(g + c), dim3(64 * v->waves), args, 0, stream));
     return SYMTILE_OK;

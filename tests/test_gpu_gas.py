@@ -973,3 +973,33 @@ def test_wg_spec_64x64_grid_larger_than_resident():
         p.run(0, WGSPEC, gemm_wgs=limit, copy_wgs=1)
     assert e.value.name == "EUNSUPPORTED"
     p.heap.barrier()
+
+
+@pytest.mark.parametrize("variant", [WGSPEC, UNFUSED], ids=VNAMES.get)
+@pytest.mark.parametrize("case", [
+    # world, M, N_local, K, tile_m, tile_n, gemm_wgs, copy_wgs
+    (1, 300, 200, 72, 64, 64, 4, 2),        # no other slot
+    (2, 300, 200, 72, 64, 64, 5, 3),        # one other slot: the consumers'
+    (3, 520, 264, 2048, 128, 128, 7, 1),    # one consumer, few slots each
+    (8, 520, 264, 40, 128, 128, 4, 9),      # more consumers than producers
+    (8, 600, 264, 8, 64, 64, 60, 40),       # one tile per producer
+    (7, 700, 264, 264, 256, 128, 2, 200),   # more consumers than tiles
+    (8, 700, 520, 520, 256, 256, 3, 2),
+], ids=lambda c: "w%d_m%d_n%d_k%d_t%dx%d_g%d_c%d" % c)
+def test_slots_shared_by_producers_and_consumers(case, variant):
+    """Whatever share of the slots the producers store themselves, every slot
+    holds the fused call's bits and each counter moves once per call."""
+    world, M, N, K, tm, tn, g, c = case
+    p = Problem(world, M, N, K, "bf16", tm, tn, seed=21)
+    r = world - 1
+    want = {r: oracle_block(p.A, p.shards[r], "bf16")}
+    p.sentinel()
+    p.run(r, FUSED)
+    p.barrier()
+    ref = u16(p.out.C_all()).copy()
+    for nt in (0, 1, 2):
+        p.sentinel()
+        p.run(r, variant, gemm_wgs=g, copy_wgs=c, nontemporal=nt)
+        p.barrier()
+        check_gathered(p, want)
+        assert np.array_equal(u16(p.out.C_all()), ref)
