@@ -65,6 +65,10 @@ __device__ __forceinline__ void store(void* p, u32x4 v, int cur, int remote,
     st16(translate(p, cur, remote, bases), v, nt);
 }
 
+// r mod world for 0 <= r < 2 * world (an integer division is some 150 cycles
+// of dependent instructions).
+__device__ __forceinline__ int wrap_rank(int r, int world) { return r >= world ? r - world : r; }
+
 // ---- buffer resources ----------------------------------------------------
 // A raw buffer resource covers [base, base + bytes); a load whose offset
 // falls outside returns zero and a store there is dropped.  The kernels use
@@ -103,8 +107,10 @@ __device__ __forceinline__ u32x4 buf_ld16(rsrc_t r, uint32_t voff, uint32_t soff
 //   kStoreNonTemporal  nt: streaming hint, the line is a preferred victim;
 //   kStoreWriteThrough sc0 sc1: system-scope coherence, written through the
 //                      L2 to memory (measured best for the cold heap copy,
-//                      where the destination is not read again soon).
-enum : int { kStoreDefault = 0, kStoreNonTemporal = 2, kStoreWriteThrough = 17 };
+//                      where the destination is not read again soon);
+//   kStoreStreamThrough sc0 sc1 nt: written through, with the streaming hint.
+enum : int { kStoreDefault = 0, kStoreNonTemporal = 2, kStoreWriteThrough = 17,
+             kStoreStreamThrough = 19 };
 
 // Load cache policies: kLoadDefault may hit a line this XCD's L2 holds from
 // before; kLoadCoherent (sc0 sc1, the encoding the memory model gives a
@@ -482,7 +488,8 @@ __device__ __forceinline__ void put_ranks(const void* p, const TileGeom& g, int 
         for (int u = 0; u < U; ++u)
             v[u] = buf_ld16p<LOAD>(rs, L.voff, (uint32_t)(b + u) * L.pass_bytes);
         for (int d = d0; d < d1; ++d) {
-            const rsrc_t rd = tile_rsrc(p, g, cur, (cur + d) % world, bases);
+            const int peer = cur + d < 2 * world ? wrap_rank(cur + d, world) : (cur + d) % world;
+            const rsrc_t rd = tile_rsrc(p, g, cur, peer, bases);
 #pragma unroll
             for (int u = 0; u < U; ++u)
                 buf_st16p<POLICY>(v[u], rd, L.voff, (uint32_t)(b + u) * L.pass_bytes);

@@ -69,12 +69,31 @@ constexpr int PD = 3;                  // prefetch distance in stages (< NS)
 
 enum KernelRole : int { ROLE_LOCAL_ONLY = 0, ROLE_FUSED = 1, ROLE_WG_SPEC = 2, ROLE_WAVE_SPEC = 3,
                         ROLE_REDUCE = 4 };
-// (UNFUSED_PC runs gas_kernel as WG_SPEC producers only, and consumer_kernel.
+// (UNFUSED_PC runs gas_pc_kernel as WG_SPEC producers only, and consumer_kernel.
 // ROLE_REDUCE runs gas_kernel<..., RED = true>, the second kernel of the
 // split-K reduction-kernel mode: no K loop, unit = (tile, band of rows), the
 // band's sum of the partials, then the epilogue.)
 
-struct GasParams {
+// Division of 0 <= n < 2^31 by a divisor the host knows: with 2^sh >= d and
+// mul = ceil(2^(31+sh) / d), which fits 32 bits, n * mul / 2^(31+sh) exceeds
+// n / d by less than 2^-sh <= 1/d, so its integer part is the quotient.  A
+// work unit's coordinates took six integer divisions of some 150 dependent
+// cycles each, before the first load of a call could be issued (700x512x1024
+// in 64x64 tiles, calls replayed from a graph: 6.4 -> 5.9 us).
+struct Div {
+    uint32_t mul, sh;
+    __device__ __forceinline__ int operator()(int n) const {
+        return (int)(((uint64_t)(uint32_t)n * mul) >> (31 + sh));
+    }
+};
+
+Div make_div(int d) {
+    uint32_t sh = 0;
+    while ((uint64_t(1) << sh) < (uint64_t)d) ++sh;
+    return Div{(uint32_t)(((uint64_t(1) << (31 + sh)) + d - 1) / d), sh};
+}
+
+struct GasCall {
     const uint16_t* A;
     const uint16_t* B;
     uint16_t* C;            // gathered output, column 0, in slot `rank`
@@ -106,13 +125,99 @@ struct GasParams {
     // stores itself, of its last tile and of the tiles before it; the
     // consumers put the others.
     int direct_last, direct_mid;
+    // by gemm_wgs, split, the tiles of a full swizzle group, the tile rows of
+    // a full and of the last group, and tiles_n (see set_divs)
+    Div by_wgs, by_split, by_width, by_rows, by_last_rows, by_tiles_n;
     // ROLE_REDUCE: bands of rows per tile (units = tiles * reduce_bands), and
     // whether the tile goes to every slot (fused) or the local one (bulk).
     int reduce_bands, reduce_all;
 };
 
+// A call as the kernels take it: 160 bytes, ordered so that what a workgroup
+// needs before its first loads lies in the first 128.  Kernel arguments are in
+// host memory, and each 64-byte line of them that a workgroup touches is a
+// round trip there (back-to-back calls, us, with the 232 bytes of GasCall ->
+// now: 500x256x2048 in 64x64 tiles 7.6 -> 7.0, tiny two-rank call 5.8 -> 5.3,
+// 64x8192x3584 in 4 slices 22.9 -> 22.1).  Everything that follows from other fields is left out,
+// small fields share words.
+struct GasParams {
+    const uint16_t* A;
+    const uint16_t* B;
+    int M, N, K, lda, ldb, tiles_m, tiles_n, gemm_wgs, group_m;
+    uint32_t mul_wgs, mul_width, mul_rows;
+    // -- 64 bytes
+    uint32_t who;           // rank, world, role, nontemporal, sk_band: 4 bits each; split: 8
+    uint32_t shifts;        // of by_wgs, by_width, by_rows, by_last_rows
+    uint32_t mul_last_rows, mul_split;
+    uint32_t share;         // direct_last, direct_mid, reduce_all: 4 bits each; reduce_bands: 8
+    uint32_t shifts2;       // of by_split, by_tiles_n
+    uint16_t* C;
+    uint32_t* arrived;
+    const uint64_t* bases;
+    uint64_t* trace;
+    uint32_t* sk_cnt;
+    // -- 128 bytes
+    uint32_t* err;
+    uint32_t* ready;
+    uint32_t epoch, spin_limit;
+    int copy_wgs;
+    uint32_t mul_tiles_n;
+};
+static_assert(sizeof(GasParams) == 160, "kernel arguments");
+
+GasParams pack(const GasCall& c) {
+    GasParams a{};
+    a.A = c.A, a.B = c.B, a.C = c.C;
+    a.M = c.M, a.N = c.N, a.K = c.K, a.lda = c.lda, a.ldb = c.ldb;
+    a.tiles_m = c.tiles_m, a.tiles_n = c.tiles_n, a.gemm_wgs = c.gemm_wgs, a.group_m = c.group_m;
+    a.mul_wgs = c.by_wgs.mul, a.mul_width = c.by_width.mul, a.mul_rows = c.by_rows.mul;
+    a.mul_last_rows = c.by_last_rows.mul, a.mul_split = c.by_split.mul;
+    a.mul_tiles_n = c.by_tiles_n.mul;
+    a.who = (uint32_t)c.rank | (uint32_t)c.world << 4 | (uint32_t)c.role << 8 |
+            (uint32_t)c.nontemporal << 12 | (uint32_t)c.sk_band << 16 | (uint32_t)c.split << 20;
+    a.shifts = c.by_wgs.sh | c.by_width.sh << 8 | c.by_rows.sh << 16 | c.by_last_rows.sh << 24;
+    a.shifts2 = c.by_split.sh | c.by_tiles_n.sh << 8;
+    a.share = (uint32_t)c.direct_last | (uint32_t)c.direct_mid << 4 |
+              (uint32_t)c.reduce_all << 8 | (uint32_t)c.reduce_bands << 12;
+    a.arrived = c.arrived, a.bases = c.bases, a.trace = c.trace, a.sk_cnt = c.sk_cnt;
+    a.err = c.err, a.ready = c.ready, a.epoch = c.epoch, a.spin_limit = c.spin_limit;
+    a.copy_wgs = c.copy_wgs;
+    return a;
+}
+
+// Bytes of the split-K counters at the start of the workspace.
+__host__ __device__ constexpr size_t sk_counter_bytes(size_t tiles) {
+    return (tiles * 8 + 255) / 256 * 256;
+}
+
+__device__ __forceinline__ GasCall unpack(const GasParams& a) {
+    GasCall c;
+    c.A = a.A, c.B = a.B, c.C = a.C;
+    c.M = a.M, c.N = a.N, c.K = a.K, c.lda = a.lda, c.ldb = a.ldb;
+    c.tiles_m = a.tiles_m, c.tiles_n = a.tiles_n, c.gemm_wgs = a.gemm_wgs, c.group_m = a.group_m;
+    c.rank = a.who & 15, c.world = a.who >> 4 & 15, c.role = a.who >> 8 & 15;
+    c.nontemporal = a.who >> 12 & 15, c.sk_band = a.who >> 16 & 15, c.split = a.who >> 20 & 255;
+    c.direct_last = a.share & 15, c.direct_mid = a.share >> 4 & 15;
+    c.reduce_all = a.share >> 8 & 15, c.reduce_bands = a.share >> 12 & 255;
+    c.by_wgs = Div{a.mul_wgs, a.shifts & 255};
+    c.by_width = Div{a.mul_width, a.shifts >> 8 & 255};
+    c.by_rows = Div{a.mul_rows, a.shifts >> 16 & 255};
+    c.by_last_rows = Div{a.mul_last_rows, a.shifts >> 24};
+    c.by_split = Div{a.mul_split, a.shifts2 & 255};
+    c.by_tiles_n = Div{a.mul_tiles_n, a.shifts2 >> 8 & 255};
+    c.arrived = a.arrived, c.bases = a.bases, c.trace = a.trace, c.sk_cnt = a.sk_cnt;
+    c.err = a.err, c.ready = a.ready, c.epoch = a.epoch, c.spin_limit = a.spin_limit;
+    c.copy_wgs = a.copy_wgs;
+    c.num_tiles = a.tiles_m * a.tiles_n;
+    c.units = c.num_tiles * (c.role == ROLE_REDUCE ? c.reduce_bands : c.split);
+    c.ldc = c.world * a.N;
+    c.sk_part = reinterpret_cast<float*>(reinterpret_cast<uint8_t*>(a.sk_cnt) +
+                                         sk_counter_bytes(c.num_tiles));
+    return c;
+}
+
 // Trace record of tile (tm, tn), or nullptr when tracing is off.
-__device__ __forceinline__ uint64_t* tile_trace(const GasParams& p, int tm, int tn) {
+__device__ __forceinline__ uint64_t* tile_trace(const GasCall& p, int tm, int tn) {
     return p.trace ? p.trace + ((size_t)tm * p.tiles_n + tn) * SYMTILE_TRACE_WORDS : nullptr;
 }
 
@@ -183,32 +288,33 @@ __device__ __forceinline__ int swz_b(int k) {
 // remap makes consecutive units land on one XCD, and the slices of a tile are
 // consecutive units, so with split-K they share that XCD's L2 (and the
 // partial tiles they exchange stay there).  Without split-K a unit is a tile.
-__device__ __forceinline__ void unit_coords(int u, int G, const GasParams& p, int& tm, int& tn,
+__device__ __forceinline__ void unit_coords(int u, int G, const GasCall& p, int& tm, int& tn,
                                             int& s) {
     int L = u;
-    const int round = u / G;
+    const int round = p.by_wgs(u);
     if ((G & 7) == 0 && (round + 1) * G <= p.units) {
         const int pos = u - round * G;
         L = round * G + (pos & 7) * (G >> 3) + (pos >> 3);
     }
     if (p.split > 1) {
-        s = L % p.split;
-        L /= p.split;
+        const int q = p.by_split(L);
+        s = L - q * p.split;
+        L = q;
     } else {
         s = 0;
     }
     const int width = p.group_m * p.tiles_n;
-    const int group = L / width;
+    const int group = p.by_width(L);
     const int first_m = group * p.group_m;
-    const int gsize = min(p.tiles_m - first_m, p.group_m);
     const int in = L - group * width;
-    tm = first_m + in % gsize;
-    tn = in / gsize;
+    const bool full = p.tiles_m - first_m >= p.group_m;
+    tn = full ? p.by_rows(in) : p.by_last_rows(in);
+    tm = first_m + in - tn * (full ? p.group_m : p.tiles_m - first_m);
 }
 
 // Producer-order tile index t -> (tile row, tile column), for schedules
 // without split-K (units == tiles).
-__device__ __forceinline__ void tile_coords(int t, int G, const GasParams& p, int& tm, int& tn) {
+__device__ __forceinline__ void tile_coords(int t, int G, const GasCall& p, int& tm, int& tn) {
     int s;
     unit_coords(t, G, p, tm, tn, s);
 }
@@ -284,33 +390,33 @@ __device__ __forceinline__ uint32_t tile_span(int rows_valid, int cols_valid, in
     return (uint32_t)(((size_t)(rows_valid - 1) * ldc + cols_valid) * 2);
 }
 
-// Store policy of the output (GasParams::nontemporal): 0 default, 1
-// non-temporal (streaming), 2 write-through (the L2 keeps no dirty line, so
-// the release fence that follows finds nothing of these stores to write
-// back).  Calls f with the cache-policy bits as a compile-time constant.
+// Store policy of the output (GasCall::nontemporal): 1 written through to
+// memory with the streaming hint, 2 written through, 0 write-back, which the
+// host picks for small unsplit fused calls only (kWriteBackTiles).  Written
+// through, the L2 keeps no dirty line of the output and the stores'
+// acknowledgement is the release; written back, each tile's release is a
+// write-back of the XCD's L2.  Calls f with the cache-policy bits as a
+// compile-time constant.
+template <typename F>
+__device__ __forceinline__ void with_through_policy(int mode, F&& f) {
+    if (mode == 1)
+        f(std::integral_constant<int, symtile::kStoreStreamThrough>{});
+    else
+        f(std::integral_constant<int, symtile::kStoreWriteThrough>{});
+}
+
 template <typename F>
 __device__ __forceinline__ void with_store_policy(int mode, F&& f) {
-    if (mode == 1)
-        f(std::integral_constant<int, symtile::kStoreNonTemporal>{});
-    else if (mode == 2)
-        f(std::integral_constant<int, symtile::kStoreWriteThrough>{});
-    else
+    if (mode == 0)
         f(std::integral_constant<int, symtile::kStoreDefault>{});
+    else
+        with_through_policy(mode, f);
 }
 
 // Release of this workgroup's output stores before their counters move
-// (agent scope): stores written through need only their acknowledgement,
-// the other policies the L2 write-back of a release fence.
-template <int POLICY>
-__device__ __forceinline__ void release_output() {
-    if constexpr (POLICY == symtile::kStoreWriteThrough)
-        symtile::release_written_through();
-    else
-        symtile::fence_release<__HIP_MEMORY_SCOPE_AGENT>();
-}
-
+// (agent scope).
 __device__ __forceinline__ void release_output(int mode) {
-    if (mode == 2)
+    if (mode != 0)
         symtile::release_written_through();
     else
         symtile::fence_release<__HIP_MEMORY_SCOPE_AGENT>();
@@ -319,7 +425,7 @@ __device__ __forceinline__ void release_output(int mode) {
 // Geometry of output tile (tm, tn) for the tile verbs: 16-bit elements, so
 // 8 per 16-byte chunk; THREADS threads cover CPR chunk columns per pass.
 template <int BM, int BN, int THREADS>
-__device__ __forceinline__ symtile::TileGeom out_tile(const GasParams& p, int tm, int tn) {
+__device__ __forceinline__ symtile::TileGeom out_tile(const GasCall& p, int tm, int tn) {
     using IO = TileIO<BM, BN, THREADS>;
     symtile::TileGeom g;
     g.rows = min(BM, p.M - tm * BM);
@@ -330,7 +436,7 @@ __device__ __forceinline__ symtile::TileGeom out_tile(const GasParams& p, int tm
 }
 
 // Address of tile (tm, tn) of this rank's column block in the local heap.
-__device__ __forceinline__ uint16_t* out_tile_ptr(const GasParams& p, int BM, int BN, int tm, int tn) {
+__device__ __forceinline__ uint16_t* out_tile_ptr(const GasCall& p, int BM, int BN, int tm, int tn) {
     return p.C + (size_t)p.rank * p.N + (size_t)tm * BM * p.ldc + (size_t)tn * BN;
 }
 
@@ -339,7 +445,7 @@ __device__ __forceinline__ uint16_t* out_tile_ptr(const GasParams& p, int BM, in
 // counters there, by THREADS threads (a workgroup or one wave).  LOAD is the
 // policy of the tile's loads (coherent after a flag_wait_coherent).
 template <int BM, int BN, int THREADS, int POLICY, int LOAD = symtile::kLoadDefault>
-__device__ void put_tile_to_peers(const GasParams& p, int tm, int tn, int tid, int d0) {
+__device__ void put_tile_to_peers(const GasCall& p, int tm, int tn, int tid, int d0) {
     using IO = TileIO<BM, BN, THREADS>;
     symtile::put_ranks<POLICY, IO::U, LOAD>(out_tile_ptr(p, BM, BN, tm, tn),
                                             out_tile<BM, BN, THREADS>(p, tm, tn), p.rank, d0,
@@ -349,11 +455,11 @@ __device__ void put_tile_to_peers(const GasParams& p, int tm, int tn, int tid, i
     else
         __builtin_amdgcn_s_waitcnt(vm_wait(0));
     if (tid < 64) {            // one wave: one release, then lane d counts slot rank + d
-        release_output<POLICY>();
+        symtile::release_written_through();
         uint32_t* flag = p.arrived + ((size_t)p.rank * p.tiles_m + tm) * p.tiles_n + tn;
         const int d = tid + d0;
         if (d < p.world)
-            symtile::flag_signal(symtile::translate(flag, p.rank, (p.rank + d) % p.world, p.bases));
+            symtile::flag_signal(symtile::translate(flag, p.rank, symtile::wrap_rank(p.rank + d, p.world), p.bases));
     }
 }
 
@@ -362,9 +468,9 @@ __device__ void put_tile_to_peers(const GasParams& p, int tm, int tn, int tid, i
 // producers' tile order, waits (bounded) until the producer's ready counter
 // reaches the epoch, acquires, and puts the tile to the heaps its producer
 // leaves to the consumers.  A
-// timed-out wait records ERR_TIMEOUT and ends this consumer.  With the
-// write-through output policy the producers' tiles are read back with
-// coherent loads, so the acquire needs no L2 invalidate.
+// timed-out wait records ERR_TIMEOUT and ends this consumer.  The producers'
+// tiles, written through, are read back with coherent loads, so the acquire
+// needs no L2 invalidate.
 //
 // A tile costs a consumer some 4 us of waiting whatever its size (the poll,
 // its loads, the acknowledgement of its stores), so tiles of up to 32 KiB are
@@ -373,7 +479,7 @@ __device__ void put_tile_to_peers(const GasParams& p, int tm, int tn, int tid, i
 // tiles, 32 consumer workgroups: 238 -> 92 us a call together with the slots
 // that the producers store themselves, see share_slots.)
 template <int BM, int BN, int THREADS>
-__device__ void consume_tiles(const GasParams& p, int cid, int ncons) {
+__device__ void consume_tiles(const GasCall& p, int cid, int ncons) {
     constexpr bool PER_WAVE = BM * BN * 2 <= 32768;
     constexpr int MOVERS = PER_WAVE ? 64 : THREADS;       // threads that move one tile
     __shared__ int s_ok;
@@ -391,8 +497,7 @@ __device__ void consume_tiles(const GasParams& p, int cid, int ncons) {
         if (tid == 0) {
             if (tr) tr[SYMTILE_TRACE_COPY_WAIT] = symtile::clock_now();
             const uint32_t* rdy = p.ready + tm * p.tiles_n + tn;
-            ok = p.nontemporal == 2 ? symtile::flag_wait_coherent(rdy, p.epoch, p.spin_limit)
-                                    : symtile::flag_wait(rdy, p.epoch, p.spin_limit);
+            ok = symtile::flag_wait_coherent(rdy, p.epoch, p.spin_limit);
             if (!ok) symtile::raise_error(p.err, symtile::ERR_TIMEOUT);
             if (tr) tr[SYMTILE_TRACE_COPY_GO] = symtile::clock_now();
             if (!PER_WAVE) s_ok = ok;
@@ -405,11 +510,9 @@ __device__ void consume_tiles(const GasParams& p, int cid, int ncons) {
             ok = s_ok;
         }
         if (!ok) return;
-        with_store_policy(p.nontemporal, [&](auto pol) {
+        with_through_policy(p.nontemporal, [&](auto pol) {
             constexpr int P = decltype(pol)::value;
-            put_tile_to_peers<BM, BN, MOVERS, P,
-                              P == symtile::kStoreWriteThrough ? symtile::kLoadCoherent
-                                                               : symtile::kLoadDefault>(
+            put_tile_to_peers<BM, BN, MOVERS, P, symtile::kLoadCoherent>(
                 p, tm, tn, tid,
                 1 + (t + p.gemm_wgs >= p.num_tiles ? p.direct_last : p.direct_mid));
         });
@@ -434,7 +537,7 @@ __device__ void consume_tiles(const GasParams& p, int cid, int ncons) {
 // barriers than that needs (small K) the wave stores each group as soon as
 // it is loaded.
 template <int BM, int BN, int POLICY>
-__device__ void copy_wave_tiles(const GasParams& p, int stages) {
+__device__ void copy_wave_tiles(const GasCall& p, int stages) {
     constexpr int CPR = staged_width(BN) / 8;   // 16-byte chunks per tile row
     constexpr int RPI = 64 / CPR;               // tile rows per wave-wide access
     constexpr int GROUPS = BM / RPI;
@@ -465,7 +568,7 @@ __device__ void copy_wave_tiles(const GasParams& p, int stages) {
 #pragma unroll
         for (int d = 1; d < MAXW; ++d)
             rd[d - 1] = symtile::make_rsrc(
-                symtile::translate(src, p.rank, (p.rank + d) % p.world, p.bases),
+                symtile::translate(src, p.rank, symtile::wrap_rank(p.rank + d, p.world), p.bases),
                 d < p.world ? span : 0u);
         const int c = lane % CPR;
         const uint32_t voff =
@@ -477,10 +580,10 @@ __device__ void copy_wave_tiles(const GasParams& p, int stages) {
         };
         auto publish = [&]() {
             __builtin_amdgcn_s_waitcnt(vm_wait(0));
-            release_output<POLICY>();                 // one release; lane d counts slot rank + d
+            symtile::release_written_through();                 // one release; lane d counts slot rank + d
             uint32_t* flag = p.arrived + ((size_t)p.rank * p.tiles_m + ptm) * p.tiles_n + ptn;
             if (lane >= 1 && lane < p.world)
-                symtile::flag_signal(symtile::translate(flag, p.rank, (p.rank + lane) % p.world,
+                symtile::flag_signal(symtile::translate(flag, p.rank, symtile::wrap_rank(p.rank + lane, p.world),
                                                         p.bases));
             if (lane == 0 && p.trace)
                 tile_trace(p, ptm, ptn)[SYMTILE_TRACE_COPY_DONE] = symtile::clock_now();
@@ -549,33 +652,41 @@ __device__ void copy_wave_tiles(const GasParams& p, int stages) {
 // tiles is not the matrix cores but the fixed cost of a stage (barrier, LDS
 // latency, issue; some 270 cycles with nothing else in it) and the loads in
 // flight, so a stage carries as much k as the LDS allows, and its code has no
-// branch.  Tiles of 64 x 64 and 128 x 128 also split each stage's k between
-// two groups of four waves: a wave then holds a square block, which halves the
-// fragment reads per MFMA against eight waves side by side, and the groups'
-// sums meet once per tile through LDS.  K loop per 64 k on full chips (w = 1,
-// 32-k ring before -> now): 64 x 64 0.366 -> 0.204 us, 128 x 128 0.635 ->
-// 0.541, 256 x 128 1.011 -> 0.885; one group instead of two 0.268 (64 x 64)
-// and 0.611 (128 x 128); fragments read two steps ahead instead of one, no
-// gain.  256-wide tiles have no LDS for three 64-k stages and keep the ring.
+// branch.  64 x 64 tiles also split each stage's k between two groups of four
+// waves: a wave then holds a square block, which cuts the fragment reads per
+// MFMA by a third against eight waves side by side, and the groups' sums meet
+// once per tile through LDS.  K loop per 64 k on full chips (w = 1, 32-k ring
+// before -> now): 64 x 64 0.366 -> 0.196 us, 128 x 128 0.635 -> 0.541, 256 x
+// 128 1.011 -> 0.875.  Two groups on 128 x 128 reach 0.509, but the exchange
+// costs 0.6 us a tile: calls with 8 to 64 stages are faster without (1400 x
+// 1024 x 512 12.5 against 12.0 us).  64 x 64 with one group: 0.219.
+// Fragments read two steps ahead instead of one: no gain.  256-wide tiles
+// have no LDS for three 64-k stages and keep the ring, and so do the smaller
+// tiles for K up to kShortK, where its small first stage starts the MFMAs
+// sooner than a deep one and there are few stages to save on (K = 256: 500 x
+// 2048 in 64 x 64 tiles 7.1 against 7.4 us, 1400 x 512 in 128 x 128 tiles 7.0
+// against 7.4; K = 512: 9.0 against 8.8 for the latter).
 struct LoopCfg {
     int kg, bk, ns;         // K groups (0: the 32-k ring), k per stage, LDS slots
     int wgm, wgn;           // waves down and across the tile after the K loop
 };
 
-constexpr LoopCfg loop_cfg(int bm, int bn, int nw, int mf) {
-    if (bm == 64 && bn == 64) return {2, 128, 4, 4, 2};
-    if (bm == 128 && bn == 128) return {2, 64, 4, 4, 2};
+constexpr LoopCfg loop_cfg(int bm, int bn, int nw, int mf, bool short_k) {
+    if (bm == 64 && bn == 64 && !short_k) return {2, 128, 4, 4, 2};
+    if (bm == 128 && bn == 128 && !short_k) return {1, 64, 4, 2, 4};
     if (bm == 256 && bn == 128) return {1, 64, 3, 4, 2};
     const int m = mf == 32 ? 2 : 4;
     return {0, BK, NS, m, nw / m};
 }
 
-template <int BM, int BN, bool BF16, int NW, int MF, bool CW = false, bool RED = false>
-__global__ __launch_bounds__(64 * (NW + CW))
-__attribute__((amdgpu_waves_per_eu(NW / 4 + CW, NW / 4 + CW)))
-void gas_kernel(const GasParams p) {
+// PC: the producers (and in one grid the consumers) of the producer-consumer
+// schedules, a kernel of its own so that the other schedules' tail, which is a
+// good part of a short call, carries none of it (0.3 us of 5.7 on the tiny
+// two-rank call: parameters reloaded and code fetched after the last store).
+template <int BM, int BN, bool BF16, int NW, int MF, bool CW, bool RED, bool SHORT, bool PC>
+__device__ __forceinline__ void gas_body(const GasCall& p) {
     constexpr int THREADS = 64 * NW;
-    constexpr LoopCfg LC = loop_cfg(BM, BN, NW, MF);
+    constexpr LoopCfg LC = loop_cfg(BM, BN, NW, MF, SHORT);
     constexpr bool DEEP = LC.kg > 0;
     constexpr int WGM = LC.wgm, WGN = LC.wgn;                 // wave grid
     constexpr int WM = BM / WGM, WN = BN / WGN;               // wave tile
@@ -592,12 +703,9 @@ void gas_kernel(const GasParams p) {
     constexpr int DA_ROW = DBK * 2, DA_BYTES = BM * DA_ROW, DB_BYTES = DBK * BNS * 2;
     constexpr int DSTAGE = DA_BYTES + DB_BYTES;
     constexpr int RING = DEEP ? LC.ns * DSTAGE : NS * STAGE;
-    // LDS of the K groups' exchange: behind the ring where that fits, else
-    // inside it, behind the staging of the epilogue
+    // the K groups' exchange lies behind the ring, so it needs no barrier before it
     constexpr int X_BYTES = KG > 1 ? BM * BN * 4 : 0;
-    constexpr bool X_APART = RING + X_BYTES <= 150 * 1024;
-    constexpr int X_AT = X_APART ? RING : C_BYTES;
-    constexpr int LDS_BYTES = X_APART ? RING + X_BYTES : RING > C_BYTES ? RING : C_BYTES;
+    constexpr int LDS_BYTES = (RING > C_BYTES ? RING : C_BYTES) + X_BYTES;
     constexpr int A_RPI = 1024 / kRowBytes;     // A rows per 1 KiB direct-to-LDS load
     constexpr int A_INSTR = BM / A_RPI / NW;    // direct-to-LDS A loads per wave per stage
     constexpr int ROWB = BNS * 2;               // bytes per staged B row (one k)
@@ -630,9 +738,11 @@ void gas_kernel(const GasParams p) {
     const int pid = blockIdx.x;
 
     // ---------------- consumer workgroups (Section 4.2.2) -----------------
-    if (p.role == ROLE_WG_SPEC && pid >= p.gemm_wgs) {
-        consume_tiles<BM, BN, THREADS>(p, pid - p.gemm_wgs, p.copy_wgs);
-        return;
+    if constexpr (PC) {
+        if (pid >= p.gemm_wgs) {
+            consume_tiles<BM, BN, THREADS>(p, pid - p.gemm_wgs, p.copy_wgs);
+            return;
+        }
     }
 
     // ---------------- producer workgroups ---------------------------------
@@ -643,7 +753,7 @@ void gas_kernel(const GasParams p) {
         // that the compiler keeps the copy wave's addressing scalar
         if (__builtin_amdgcn_readfirstlane(wave) == NW) {
             const int stages = DEEP ? (KT_all * BK + DBK - 1) / DBK : KT_all;
-            with_store_policy(p.nontemporal, [&](auto pol) {
+            with_through_policy(p.nontemporal, [&](auto pol) {
                 copy_wave_tiles<BM, BN, decltype(pol)::value>(p, stages);
             });
             return;
@@ -685,16 +795,16 @@ void gas_kernel(const GasParams p) {
         int tm, tn, ks;
         if (reducer) {
             // unit = (tile, band); ks is the band (no K slice: KT = 0 below)
-            const int tile = t / p.reduce_bands;
+            const int tile = t >> __builtin_ctz(p.reduce_bands);   // a power of two
             ks = t - tile * p.reduce_bands;
-            tm = tile / p.tiles_n;
+            tm = p.by_tiles_n(tile);
             tn = tile - tm * p.tiles_n;
         } else {
             unit_coords(t, G, p, tm, tn, ks);
         }
         // this unit's K slice: stages [kt0, kt0 + KT)
-        const int kt0 = reducer ? 0 : ks * KT_all / p.split;
-        const int KT = reducer ? 0 : (ks + 1) * KT_all / p.split - kt0;
+        const int kt0 = reducer ? 0 : p.by_split(ks * KT_all);
+        const int KT = reducer ? 0 : p.by_split((ks + 1) * KT_all) - kt0;
         // (the trace record's address is recomputed at each event so that
         // nothing extra stays live across the K loop)
         if (p.trace && tid == 0 && ks == 0 && !reducer) {
@@ -1097,11 +1207,10 @@ void gas_kernel(const GasParams p) {
             if constexpr (KG == 2) {
                 // Sum of the two groups' products: group g keeps block rows
                 // g*MI .. g*MI + MI-1 of the block both hold, and hands the
-                // others over through LDS (behind the staging of the epilogue).
+                // others over through LDS.
                 constexpr int G4 = MI * NI * (ACC_N / 4);
-                static_assert(NW * G4 * 1024 == X_BYTES && X_AT + X_BYTES <= LDS_BYTES, "exchange");
-                uint8_t* X = smem + X_AT;
-                if constexpr (!X_APART) __syncthreads();   // every wave is done with the ring
+                static_assert(NW * G4 * 1024 == X_BYTES, "exchange");
+                uint8_t* X = smem + LDS_BYTES - X_BYTES;
 #pragma unroll
                 for (int i = 0; i < MI; ++i)
 #pragma unroll
@@ -1565,7 +1674,7 @@ void gas_kernel(const GasParams p) {
 
         // FUSED: every slot.  WAVE_SPEC: the local slot (the copy wave does the
         // rest during the next tile), except for this workgroup's last tile.
-        const int n_dst = (p.role == ROLE_FUSED || (reducer && p.reduce_all) ||
+        const int n_dst = ((!PC && p.role == ROLE_FUSED) || (reducer && p.reduce_all) ||
                            (CW && t + G >= p.num_tiles))
                               ? p.world
                               : 1;
@@ -1599,7 +1708,7 @@ void gas_kernel(const GasParams p) {
                         crow + min(b + u, IO::PASSES - 1) * IO::RP * CROW);
                 for (int d = d_lo; d < d_hi; ++d) {
                     const symtile::rsrc_t rd =
-                        symtile::tile_rsrc(tile_local, geom, p.rank, (p.rank + d) % p.world, p.bases);
+                        symtile::tile_rsrc(tile_local, geom, p.rank, symtile::wrap_rank(p.rank + d, p.world), p.bases);
                     with_store_policy(p.nontemporal, [&](auto pol) {
 #pragma unroll
                         for (int u = 0; u < IO::U; ++u)
@@ -1621,7 +1730,7 @@ void gas_kernel(const GasParams p) {
                     // past the band count means the workspace was not zero when
                     // the call started: the data stored is this call's, but the
                     // tile is not published, and the error is reported.
-                    release_output(p.nontemporal);
+                    symtile::release_written_through();
                     uint32_t* cnt = p.sk_cnt + 2 * (tm * p.tiles_n + tn);
                     uint32_t u = 0;
                     if (tid == 0) {
@@ -1633,8 +1742,7 @@ void gas_kernel(const GasParams p) {
                     const uint32_t w1 = __shfl(red_cnt1, 0);
                     publish = w1 == 0 && u == (uint32_t)p.reduce_bands - 1u;
                     if (publish) {
-                        if (p.nontemporal != 2) symtile::fence_acquire<__HIP_MEMORY_SCOPE_AGENT>();
-                        if (tid == 0)
+                            if (tid == 0)
                             symtile::atomic_xchg<__ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT>(cnt, 0u);
                     }
                 } else if (banded) {
@@ -1644,7 +1752,7 @@ void gas_kernel(const GasParams p) {
                     // split); the one that draws 2*split - 1 acquires the others'
                     // stores, resets the counters for the next call and publishes
                     // the tile's counters behind a release of its own.
-                    release_output(p.nontemporal);
+                    symtile::release_written_through();
                     uint32_t* cnt = p.sk_cnt + 2 * (tm * p.tiles_n + tn);
                     uint32_t u2 = 0;
                     if (tid == 0)
@@ -1655,8 +1763,7 @@ void gas_kernel(const GasParams p) {
                         // the other slices' band stores happen before the counters
                         // move: written through, they were in memory before their
                         // slices' tickets; otherwise acquire their releases
-                        if (p.nontemporal != 2) symtile::fence_acquire<__HIP_MEMORY_SCOPE_AGENT>();
-                        if (tid == 0) {
+                            if (tid == 0) {
                             symtile::atomic_xchg<__ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT>(cnt, 0u);
                             symtile::atomic_xchg<__ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT>(cnt + 1, 0u);
                         }
@@ -1668,20 +1775,42 @@ void gas_kernel(const GasParams p) {
                     release_output(p.nontemporal);
                     uint32_t* flag = p.arrived + ((size_t)p.rank * p.tiles_m + tm) * p.tiles_n + tn;
                     if (tid >= d_lo && tid < d_hi)
-                        symtile::flag_signal(symtile::translate(flag, p.rank, (p.rank + tid) % p.world, p.bases));
+                        symtile::flag_signal(symtile::translate(flag, p.rank, symtile::wrap_rank(p.rank + tid, p.world), p.bases));
                     if (tid == 0 && p.role == ROLE_WG_SPEC && d_lo == 0)
                         symtile::flag_signal(p.ready + tm * p.tiles_n + tn);
                     if (p.trace && tid == 0) tile_trace(p, tm, tn)[SYMTILE_TRACE_RELEASED] = symtile::clock_now();
                 }
             }
-            const int direct = p.role != ROLE_WG_SPEC || d_lo > 0 ? 0
-                               : t + G >= p.num_tiles             ? p.direct_last
-                                                                  : p.direct_mid;
+            if (!PC || d_lo > 0) break;
+            const int direct = t + G >= p.num_tiles ? p.direct_last : p.direct_mid;
             if (direct == 0) break;
             d_lo = 1;
             d_hi = 1 + direct;
         }
     }
+}
+
+template <int BM, int BN, bool BF16, int NW, int MF, bool CW = false, bool RED = false>
+__global__ __launch_bounds__(64 * (NW + CW))
+__attribute__((amdgpu_waves_per_eu(NW / 4 + CW, NW / 4 + CW)))
+void gas_kernel(const GasParams a) {
+    gas_body<BM, BN, BF16, NW, MF, CW, RED, false, false>(unpack(a));
+}
+
+// WG_SPEC, and the producers of UNFUSED_PC.
+template <int BM, int BN, bool BF16, int NW, int MF, bool SHORT>
+__global__ __launch_bounds__(64 * NW)
+__attribute__((amdgpu_waves_per_eu(NW / 4, NW / 4)))
+void gas_pc_kernel(const GasParams a) {
+    gas_body<BM, BN, BF16, NW, MF, false, false, SHORT, true>(unpack(a));
+}
+
+// The 32-k ring for short K (see loop_cfg).
+template <int BM, int BN, bool BF16, int NW>
+__global__ __launch_bounds__(64 * NW)
+__attribute__((amdgpu_waves_per_eu(NW / 4, NW / 4)))
+void gas_short_kernel(const GasParams a) {
+    gas_body<BM, BN, BF16, NW, 32, false, false, true, false>(unpack(a));
 }
 
 // Copy kernels of the bulk-synchronous and unfused producer-consumer
@@ -1692,13 +1821,14 @@ constexpr int copy_threads() { return BM >= 128 ? 1024 : 256; }
 
 // Second kernel of the bulk-synchronous schedule (Section 4.1.1).
 template <int BM, int BN>
-__global__ __launch_bounds__(copy_threads<BM>()) void scatter_kernel(const GasParams p) {
+__global__ __launch_bounds__(copy_threads<BM>()) void scatter_kernel(const GasParams a) {
+    const GasCall p = unpack(a);
     for (int t = blockIdx.x; t < p.num_tiles; t += gridDim.x) {
-        const int tm = t / p.tiles_n, tn = t % p.tiles_n;
+        const int tm = p.by_tiles_n(t), tn = t - tm * p.tiles_n;
         uint64_t* tr = tile_trace(p, tm, tn);
         if (tr && threadIdx.x == 0)
             tr[SYMTILE_TRACE_COPY_WAIT] = tr[SYMTILE_TRACE_COPY_GO] = symtile::clock_now();
-        with_store_policy(p.nontemporal, [&](auto pol) {
+        with_through_policy(p.nontemporal, [&](auto pol) {
             put_tile_to_peers<BM, BN, copy_threads<BM>(), decltype(pol)::value>(p, tm, tn,
                                                                                 threadIdx.x, 1);
         });
@@ -1709,17 +1839,19 @@ __global__ __launch_bounds__(copy_threads<BM>()) void scatter_kernel(const GasPa
 // Copy kernel of the unfused producer-consumer schedule (Section 4.1.2):
 // runs on its own stream next to the producer grid of gas_kernel.
 template <int BM, int BN>
-__global__ __launch_bounds__(copy_threads<BM>()) void consumer_kernel(const GasParams p) {
-    consume_tiles<BM, BN, copy_threads<BM>()>(p, blockIdx.x, gridDim.x);
+__global__ __launch_bounds__(copy_threads<BM>()) void consumer_kernel(const GasParams a) {
+    consume_tiles<BM, BN, copy_threads<BM>()>(unpack(a), blockIdx.x, gridDim.x);
 }
 
 // ---------------------------------------------------------------------------
 struct Variant {
     int bm, bn;
     bool bf16;
+    bool short_k;                // for unsplit calls with K <= kShortK only
     int waves;                   // of the build
     int asked;                   // wave counts that select it, as a sum of 4 and 8
     const void* gas;
+    const void* gas_pc;          // the same for WG_SPEC and UNFUSED_PC
     const void* scatter;
     const void* consumer;
     int copy_threads;            // workgroup size of scatter_kernel and consumer_kernel
@@ -1747,8 +1879,9 @@ const void* wave_spec_kernel() {
 
 template <int BM, int BN, bool BF16, int NW, int MF = 32, int ASKED = NW, bool WS = false>
 Variant make_variant() {
-    return Variant{BM, BN, BF16, NW, ASKED,
+    return Variant{BM, BN, BF16, false, NW, ASKED,
                    reinterpret_cast<const void*>(&gas_kernel<BM, BN, BF16, NW, MF>),
+                   reinterpret_cast<const void*>(&gas_pc_kernel<BM, BN, BF16, NW, MF, false>),
                    reinterpret_cast<const void*>(&scatter_kernel<BM, BN>),
                    reinterpret_cast<const void*>(&consumer_kernel<BM, BN>),
                    copy_threads<BM>(), wave_spec_kernel<BM, BN, BF16, NW, MF, WS>(),
@@ -1756,9 +1889,36 @@ Variant make_variant() {
                    band_quantum<BM, BN, MF>()};
 }
 
-// waves == 0 picks the first entry of the shape (the default wave count).
-const Variant* find_variant(int bm, int bn, bool bf16, int waves) {
+template <int BM, int BN, bool BF16, int NW, int ASKED>
+Variant make_short_variant() {
+    return Variant{BM, BN, BF16, true, NW, ASKED,
+                   reinterpret_cast<const void*>(&gas_short_kernel<BM, BN, BF16, NW>),
+                   reinterpret_cast<const void*>(&gas_pc_kernel<BM, BN, BF16, NW, 32, true>),
+                   reinterpret_cast<const void*>(&scatter_kernel<BM, BN>),
+                   reinterpret_cast<const void*>(&consumer_kernel<BM, BN>),
+                   copy_threads<BM>(), nullptr, nullptr, band_quantum<BM, BN, 32>()};
+}
+
+constexpr int kShortK = 256;
+
+// Tiles per rank up to which the library's choice of store policy (0) writes
+// back.  A write-through store is acknowledged by memory, later than by the
+// L2, and the more slots a tile is stored to, the longer that takes, once per
+// call; the release of write-back stores walks the L2 once per tile, and an
+// XCD's tiles (one in eight) pay one after another.  K = 256, 64x64 tiles,
+// write-back / written through, us: w = 2, 16 tiles 5.95 / 5.96, 64 tiles 6.33
+// / 6.03; w = 8, 4 tiles 7.27 / 8.25, 64 tiles 8.11 / 8.53.  With many tiles
+// (fp16 8192x512x1024, w = 8): fused 121 / 69, bulk-synchronous 157 / 74,
+// WG_SPEC 268 / 99.
+constexpr size_t kWriteBackTiles = 8;
+
+// waves == 0 picks the first entry of the shape (the default wave count);
+// short_k prefers the shape's build for short K, where it has one.
+const Variant* find_variant(int bm, int bn, bool bf16, int waves, bool short_k = false) {
     static const Variant table[] = {
+        make_short_variant<64, 64, false, 4, 4>(), make_short_variant<64, 64, true, 4, 4>(),
+        make_short_variant<128, 128, false, 8, 4 + 8>(),
+        make_short_variant<128, 128, true, 8, 4 + 8>(),
         make_variant<64, 64, false, 8, 16, 4>(), make_variant<64, 64, true, 8, 16, 4>(),
         make_variant<128, 128, false, 8, 32, 4 + 8>(), make_variant<128, 128, true, 8, 32, 4 + 8>(),
         make_variant<256, 128, false, 8, 32, 4 + 8, true>(),
@@ -1768,7 +1928,8 @@ const Variant* find_variant(int bm, int bn, bool bf16, int waves) {
         make_variant<256, 224, false, 8, 16>(), make_variant<256, 224, true, 8, 16>(),
     };
     for (const Variant& v : table)
-        if (v.bm == bm && v.bn == bn && v.bf16 == bf16 && (waves == 0 || (v.asked & waves)))
+        if (v.bm == bm && v.bn == bn && v.bf16 == bf16 && (short_k || !v.short_k) &&
+            (waves == 0 || (v.asked & waves)))
             return &v;
     return nullptr;
 }
@@ -1787,8 +1948,8 @@ const Variant* find_wave_spec_variant(int bm, int bn, bool bf16) {
 // for 64 x 64 tiles, whose deep LDS ring leaves room for one workgroup per CU
 // where its 32 KiB predecessor left room for four: larger grids are accepted
 // as before and run as a resident grid that takes more tiles per workgroup.
-symtile_status coresident_limit(const Variant* v, int device, int* cus, int* limit,
-                                int* resident) {
+symtile_status coresident_limit(const Variant* v, const void* kernel, int device, int* cus,
+                                int* limit, int* resident) {
     int n_cu = symtile_host::cu_count(device);
     if (n_cu <= 0) return symtile_host::fail(SYMTILE_EHIP, "cannot read the CU count");
     // workgroups of a kernel per CU: fixed for the process, so asked once per
@@ -1798,13 +1959,13 @@ symtile_status coresident_limit(const Variant* v, int device, int* cus, int* lim
     int per_cu = 0;
     {
         std::lock_guard<std::mutex> lock(mu);
-        auto it = per_cu_known.find({v->gas, device});
+        auto it = per_cu_known.find({kernel, device});
         if (it != per_cu_known.end()) per_cu = it->second;
     }
     if (per_cu == 0) {
-        SYMTILE_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, v->gas, 64 * v->waves, 0));
+        SYMTILE_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, 64 * v->waves, 0));
         std::lock_guard<std::mutex> lock(mu);
-        per_cu_known[{v->gas, device}] = per_cu;
+        per_cu_known[{kernel, device}] = per_cu;
     }
     *cus = n_cu;
     *resident = per_cu * n_cu;
@@ -1813,7 +1974,7 @@ symtile_status coresident_limit(const Variant* v, int device, int* cus, int* lim
 }
 
 // Producer-consumer schedules: the slots a producer stores itself
-// (GasParams::direct_last, direct_mid).
+// (GasCall::direct_last, direct_mid).
 //
 // Last tiles.  All producers finish their last tile at about the same time
 // and then have nothing to do, while a consumer workgroup moves some 50 GB/s:
@@ -1826,7 +1987,7 @@ symtile_status coresident_limit(const Variant* v, int device, int* cus, int* lim
 // tile's K loop, at 50 GB/s per workgroup and 4.5 TFLOP/s per producer (what
 // both reach on the large shapes), and at least one slot; the producers
 // store the rest, which would only queue up behind the consumers.
-void share_slots(GasParams& p, int bm, int bn, int g, int c) {
+void share_slots(GasCall& p, int bm, int bn, int g, int c) {
     const int others = p.world - 1;
     p.direct_last = p.direct_mid = 0;
     if (others <= 1) return;
@@ -1838,10 +1999,19 @@ void share_slots(GasParams& p, int bm, int bn, int g, int c) {
     p.direct_mid = others - (int)std::min(std::max(slots, 1.0), (double)others);
 }
 
+// The divisors of a call, once everything else is set.
+void set_divs(GasCall& p) {
+    p.by_wgs = make_div(p.gemm_wgs);
+    p.by_split = make_div(p.split);
+    p.by_width = make_div(p.group_m * p.tiles_n);
+    p.by_rows = make_div(p.group_m);
+    p.by_last_rows = make_div(p.tiles_m % p.group_m ? p.tiles_m % p.group_m : p.group_m);
+    p.by_tiles_n = make_div(p.tiles_n);
+}
+
 // Split-K workspace: two counters per tile, rounded up to 256 bytes, then
 // `split` fp32 partial tiles per tile.
 constexpr int kMaxSplit = 64;
-size_t sk_counter_bytes(size_t tiles) { return (tiles * 8 + 255) / 256 * 256; }
 size_t sk_workspace_bytes(size_t tiles, int bm, int bn, int split) {
     return split <= 1 ? 0 : sk_counter_bytes(tiles) + tiles * split * (size_t)bm * bn * 4;
 }
@@ -1905,7 +2075,7 @@ extern "C" symtile_status symtile_device_info(int device, int tile_m, int tile_n
     const Variant* v = find_variant(tile_m, tile_n, true, 0);
     if (!v) return symtile_host::fail(SYMTILE_EUNSUPPORTED, "tile shape not built");
     int cus = 0, lim = 0, resident = 0;
-    if (symtile_status st = coresident_limit(v, device, &cus, &lim, &resident)) return st;
+    if (symtile_status st = coresident_limit(v, v->gas_pc, device, &cus, &lim, &resident)) return st;
     if (cu_count) *cu_count = cus;
     if (max_coresident_wgs) *max_coresident_wgs = lim;
     return SYMTILE_OK;
@@ -1952,7 +2122,8 @@ extern "C" symtile_status symtile_gemm_all_scatter(
     if (waves == 0 && cfg.tile_m == 256 && cfg.tile_n == 256 && split == 1 &&
         (cfg.variant == SYMTILE_FUSED_SEQ || cfg.variant == SYMTILE_BULK_SYNC))
         waves = 4;
-    const Variant* v = find_variant(cfg.tile_m, cfg.tile_n, dtype == SYMTILE_BF16, waves);
+    const Variant* v = find_variant(cfg.tile_m, cfg.tile_n, dtype == SYMTILE_BF16, waves,
+                                    split == 1 && K <= kShortK);
     if (!v) return fail(SYMTILE_EUNSUPPORTED, "tile shape / wave count not built");
     // Buffer resources span one tile row band of A or C and the whole of B;
     // each must stay below 2 GiB.
@@ -1984,7 +2155,8 @@ extern "C" symtile_status symtile_gemm_all_scatter(
         if (f0 < c0 + c_bytes && c0 < f0 + flag_bytes)
             return fail(SYMTILE_EINVAL, "arrived_local overlaps C_gathered_local");
     }
-    if ((cfg.variant == SYMTILE_WG_SPEC || cfg.variant == SYMTILE_UNFUSED_PC) && !ready)
+    const bool pc = cfg.variant == SYMTILE_WG_SPEC || cfg.variant == SYMTILE_UNFUSED_PC;
+    if (pc && !ready)
         return fail(SYMTILE_EINVAL, "WG_SPEC and UNFUSED_PC need a ready counter array");
     if (reinterpret_cast<uintptr_t>(cfg.trace) % 8)
         return fail(SYMTILE_EINVAL, "trace must be 8-byte aligned");
@@ -2011,9 +2183,11 @@ extern "C" symtile_status symtile_gemm_all_scatter(
     }
 
     int cus = 0, limit = 0, resident = 0;
-    if (symtile_status st = coresident_limit(v, h->device, &cus, &limit, &resident)) return st;
+    if (symtile_status st =
+            coresident_limit(v, pc ? v->gas_pc : v->gas, h->device, &cus, &limit, &resident))
+        return st;
 
-    GasParams p;
+    GasCall p;
     p.A = static_cast<const uint16_t*>(A);
     p.B = static_cast<const uint16_t*>(B_shard);
     p.C = static_cast<uint16_t*>(C_gathered_local);
@@ -2032,12 +2206,15 @@ extern "C" symtile_status symtile_gemm_all_scatter(
     p.tiles_m = tiles_m;
     p.tiles_n = tiles_n;
     p.num_tiles = (int)num_tiles;
-    p.group_m = cfg.group_m;
+    p.group_m = std::min(cfg.group_m, tiles_m);
     p.epoch = cfg.epoch;
     p.spin_limit = cfg.spin_limit;
-    p.nontemporal = cfg.nontemporal;
     if (cfg.nontemporal < 0 || cfg.nontemporal > 2)
         return fail(SYMTILE_EINVAL, "nontemporal must be 0, 1 or 2");
+    p.nontemporal = cfg.nontemporal;
+    if (cfg.nontemporal == 0 && (cfg.variant != SYMTILE_FUSED_SEQ || split > 1 ||
+                                 num_tiles > kWriteBackTiles * world_size))
+        p.nontemporal = 2;
     p.trace = cfg.trace;
     p.copy_wgs = 0;
     p.split = split;
@@ -2094,14 +2271,16 @@ extern "C" symtile_status symtile_gemm_all_scatter(
                 p.sk_band = 2;
         }
         p.role = cfg.variant == SYMTILE_FUSED_SEQ ? ROLE_FUSED : ROLE_LOCAL_ONLY;
-        void* args[] = {&p};
+        set_divs(p);
+        GasParams packed = pack(p);
+        void* args[] = {&packed};
         SYMTILE_HIP(hipLaunchKernel(v->gas, dim3(g), dim3(64 * v->waves), args, 0, stream));
         if (p.sk_band == 2) {
             // Reduction kernel: every (tile, band of rows) sums its rows of
             // the partials in slice order and stores them.  Bands: the most
             // (a power of two, whole accumulator blocks and store passes)
             // that keep the grid within the CU count.
-            GasParams r = p;
+            GasCall r = p;
             int nb = 1;
             while (cfg.tile_m % (2 * nb) == 0 && (cfg.tile_m / (2 * nb)) % v->band_q == 0 &&
                    (size_t)ntiles * 2 * nb <= (size_t)cus)
@@ -2112,7 +2291,8 @@ extern "C" symtile_status symtile_gemm_all_scatter(
             r.reduce_all = cfg.variant == SYMTILE_FUSED_SEQ;
             r.units = ntiles * nb;
             r.gemm_wgs = std::min(r.units, cus);
-            void* rargs[] = {&r};
+            GasParams rpacked = pack(r);
+            void* rargs[] = {&rpacked};
             SYMTILE_HIP(hipLaunchKernel(v->reduce, dim3(r.gemm_wgs), dim3(64 * v->waves), rargs, 0,
                                         stream));
         }
@@ -2136,7 +2316,9 @@ extern "C" symtile_status symtile_gemm_all_scatter(
         g = std::min(g, ntiles);
         p.gemm_wgs = g;
         p.role = ROLE_WAVE_SPEC;
-        void* args[] = {&p};
+        set_divs(p);
+        GasParams packed = pack(p);
+        void* args[] = {&packed};
         SYMTILE_HIP(hipLaunchKernel(ws->gas_ws, dim3(g), dim3(64 * (ws->waves + 1)), args, 0,
                                     stream));
         return SYMTILE_OK;
@@ -2165,10 +2347,12 @@ extern "C" symtile_status symtile_gemm_all_scatter(
         p.copy_wgs = std::min(c, ntiles);
         p.role = ROLE_WG_SPEC;
         share_slots(p, cfg.tile_m, cfg.tile_n, g, p.copy_wgs);
-        void* args[] = {&p};
+        set_divs(p);
+        GasParams packed = pack(p);
+        void* args[] = {&packed};
         SYMTILE_HIP(hipEventRecord(h->ev_fork, stream));
         SYMTILE_HIP(hipStreamWaitEvent(cs, h->ev_fork, 0));
-        SYMTILE_HIP(hipLaunchKernel(v->gas, dim3(g), dim3(64 * v->waves), args, 0, stream));
+        SYMTILE_HIP(hipLaunchKernel(v->gas_pc, dim3(g), dim3(64 * v->waves), args, 0, stream));
         SYMTILE_HIP(hipLaunchKernel(v->consumer, dim3(p.copy_wgs), dim3(v->copy_threads),
                                     args, 0, cs));
         SYMTILE_HIP(hipEventRecord(h->ev_join, cs));
@@ -2193,8 +2377,10 @@ extern "C" symtile_status symtile_gemm_all_scatter(
     p.copy_wgs = c;
     p.role = ROLE_WG_SPEC;
     share_slots(p, cfg.tile_m, cfg.tile_n, g, std::min(c, ntiles));
-    void* args[] = {&p};
-    SYMTILE_HIP(hipLaunchKernel(v->gas, dim3(g + c), dim3(64 * v->waves), args, 0, stream));
+    set_divs(p);
+    GasParams packed = pack(p);
+    void* args[] = {&packed};
+    SYMTILE_HIP(hipLaunchKernel(v->gas_pc, dim3(g + c), dim3(64 * v->waves), args, 0, stream));
     return SYMTILE_OK;
 }
 

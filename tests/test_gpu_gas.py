@@ -1003,3 +1003,31 @@ def test_slots_shared_by_producers_and_consumers(case, variant):
         p.barrier()
         check_gathered(p, want)
         assert np.array_equal(u16(p.out.C_all()), ref)
+
+
+@pytest.mark.parametrize("case", [
+    # world, M, N_local, group_m, gemm_wgs: tile rows that the swizzle groups do not divide
+    (2, 64 * 9, 64 * 3, 4, 0),
+    (2, 64 * 7, 64 * 5, 5, 8),
+    (1, 64 * 5, 64 * 7, 1000000, 16),      # one group, larger than the grid of tiles
+    (3, 64 * 11, 64, 3, 24),
+    (8, 64, 64 * 17, 2, 0),
+], ids=lambda c: "w%d_m%d_n%d_gm%d_g%d" % c)
+@pytest.mark.parametrize("K", [256, 264], ids=["short_loop", "deep_loop"])
+def test_tile_mapping_covers_every_tile_once(case, K):
+    """Every tile of every slot is written and counted once, whatever the swizzle
+    group and grid, on both sides of the K at which the small tiles change loop,
+    and with each store policy (the default one on both sides of its own limit)."""
+    world, M, N, gm, g = case
+    p = Problem(world, M, N, K, "f16", 64, 64, seed=M + N)
+    want = {0: oracle_block_bounded(p.A, p.shards[0], "f16")}
+    for nt in (0, 1, 2):
+        p.sentinel()
+        p.run(0, FUSED, group_m=gm, gemm_wgs=g, nontemporal=nt)
+        p.barrier()
+        check_gathered(p, want)
+    for split in (2, 3):
+        p.sentinel()
+        p.run(0, FUSED, group_m=gm, split_k=split)
+        p.barrier()
+        check_gathered(p, want)
