@@ -74,24 +74,8 @@ enum KernelRole : int { ROLE_LOCAL_ONLY = 0, ROLE_FUSED = 1, ROLE_WG_SPEC = 2, R
 // split-K reduction-kernel mode: no K loop, unit = (tile, band of rows), the
 // band's sum of the partials, then the epilogue.)
 
-// Division of 0 <= n < 2^31 by a divisor the host knows: with 2^sh >= d and
-// mul = ceil(2^(31+sh) / d), which fits 32 bits, n * mul / 2^(31+sh) exceeds
-// n / d by less than 2^-sh <= 1/d, so its integer part is the quotient.  A
-// work unit's coordinates took six integer divisions of some 150 dependent
-// cycles each, before the first load of a call could be issued (700x512x1024
-// in 64x64 tiles, calls replayed from a graph: 6.4 -> 5.9 us).
-struct Div {
-    uint32_t mul, sh;
-    __device__ __forceinline__ int operator()(int n) const {
-        return (int)(((uint64_t)(uint32_t)n * mul) >> (31 + sh));
-    }
-};
-
-Div make_div(int d) {
-    uint32_t sh = 0;
-    while ((uint64_t(1) << sh) < (uint64_t)d) ++sh;
-    return Div{(uint32_t)(((uint64_t(1) << (31 + sh)) + d - 1) / d), sh};
-}
+using symtile_host::Div;
+using symtile_host::make_div;
 
 struct GasCall {
     const uint16_t* A;

@@ -34,6 +34,25 @@ struct symtile_heap {
 
 namespace symtile_host {
 
+// Division of 0 <= n < 2^31 by a divisor the host knows: with 2^sh >= d and
+// mul = ceil(2^(31+sh) / d), which fits 32 bits, n * mul / 2^(31+sh) exceeds
+// n / d by less than 2^-sh <= 1/d, so its integer part is the quotient.  A
+// work unit's coordinates took six integer divisions of some 150 dependent
+// cycles each, before the first load of a call could be issued (700x512x1024
+// in 64x64 tiles, calls replayed from a graph: 6.4 -> 5.9 us).
+struct Div {
+    uint32_t mul, sh;
+    __device__ __forceinline__ int operator()(int n) const {
+        return (int)(((uint64_t)(uint32_t)n * mul) >> (31 + sh));
+    }
+};
+
+inline Div make_div(int d) {
+    uint32_t sh = 0;
+    while ((uint64_t(1) << sh) < (uint64_t)d) ++sh;
+    return Div{(uint32_t)(((uint64_t(1) << (31 + sh)) + d - 1) / d), sh};
+}
+
 // Record `msg` as this thread's last error and return `st`.
 symtile_status fail(symtile_status st, const std::string& msg);
 symtile_status ok();

@@ -6,17 +6,13 @@
 // and the post-state is the same; what differs is which side's addresses are
 // translated (the remote read of a get, the remote write of a put).
 //
-// Data path: HBM-bound.  Each workgroup owns a run of tiles_per_wg
-// consecutive (rank, tile) items; every thread moves 16-byte chunks,
+// Data path: HBM-bound.  A workgroup owns a run of adjacent tiles of one tile
+// row, copied as one rectangle, row by row, so the memory sees long row
+// segments instead of many short ones; every thread moves 16-byte chunks,
 // issuing a batch of loads before the matching stores so many requests are
-// in flight per wave.  Consecutive lanes take consecutive chunks of a tile
-// row, so each wave instruction covers whole cache lines.  After its run the
-// workgroup publishes all of its counters behind one agent-scope release:
-// the release is an L2 write-back, serialised per XCD, so its count (not the
-// data path) bounds the kernel when every tile pays for one.  A run of
-// adjacent tiles of one tile row is copied as one rectangle, row by row, so
-// the memory sees long row segments instead of many short ones.  Stores are
-// written through to memory (cold copies measured fastest that way).
+// in flight per wave.  Stores are written through to memory (cold copies
+// measured fastest that way), so their acknowledgement is the release and the
+// run's counters follow it.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -29,10 +25,11 @@
 namespace {
 
 using symtile::u32x4;
+using symtile_host::Div;
+using symtile_host::make_div;
 
-// Workgroup shape: one wide workgroup per CU keeps the number of releases
-// (one per workgroup) small while 16 waves per CU keep enough loads in
-// flight to cover HBM latency.
+// Workgroup shape: 16 waves of one wide workgroup keep enough loads in flight
+// per CU to cover HBM latency.
 #ifndef SYMTILE_COPY_THREADS
 #define SYMTILE_COPY_THREADS 1024
 #endif
@@ -42,42 +39,58 @@ using symtile::u32x4;
 constexpr int kThreads = SYMTILE_COPY_THREADS;
 constexpr int kBatch = SYMTILE_COPY_BATCH;   // chunks in flight per thread
 
+// (What the rectangle kernel needs lies in the first 108 bytes, two 64-byte
+// lines: kernel arguments are in host memory, and a workgroup waits for every
+// line of them that it touches.)
 struct CopyParams {
     const uint64_t* bases;
-    int world, shift, only_rank;
-    int mode;                // SYMTILE_PUT or SYMTILE_GET
-    uint64_t src_off, dst_off, flag_off;
+    uint64_t src_off, dst_off;
     int rows;                // matrix rows
     int row_chunks;          // 16-byte chunks per matrix row
     int ld_bytes;            // row stride in bytes
     int tile_r;              // tile rows
     int tile_chunks;         // 16-byte chunks per tile row
+    int tiles_r;             // tile rows of the matrix
+    // Rectangle runs (segs > 0): each tile row is cut into segs runs of
+    // seg_tiles tiles, the first seg_more of them one more.
+    int segs, seg_tiles, seg_more;
+    uint32_t who;            // world, shift (in [0, world)), only_rank + 1, mode: 4 bits each
+    Div by_segs, by_tiles_r;
+    // A pass of the workgroup covers kThreads chunks of rectangles up to width
+    // chunks wide: lg_w >= 0, 1 << lg_w chunk columns; else row-major through
+    // the rectangle.
+    int width, lg_w;
+    Div by_width;
+    uint64_t flag_off;
     int tiles_c;             // tiles per matrix row of tiles
-    int ntiles;              // tiles per rank
-    int nitems;              // (rank, tile) items of this launch
-    int per_wg;              // consecutive items per workgroup
-    int band_lg_w;           // >= 0: each run is one rectangle, 1 << band_lg_w chunks wide
+    // Otherwise workgroup g takes the (rank, tile) items [g * per_wg, ...).
+    int nitems, per_wg, ntiles;
+    Div by_ntiles, by_tiles_c;
+
+    __device__ __forceinline__ int world() const { return who & 15; }
+    __device__ __forceinline__ int shift() const { return who >> 4 & 15; }
+    __device__ __forceinline__ int only_rank() const { return (int)(who >> 8 & 15) - 1; }
+    __device__ __forceinline__ int mode() const { return who >> 12 & 15; }
 };
 
 // Source and destination ranks of executing rank r.
 __device__ __forceinline__ void copy_ranks(const CopyParams& p, int r, int& src, int& dst) {
-    const int peer_up = ((r + p.shift) % p.world + p.world) % p.world;
-    const int peer_down = ((r - p.shift) % p.world + p.world) % p.world;
-    src = (p.mode == SYMTILE_GET) ? peer_down : r;
-    dst = (p.mode == SYMTILE_GET) ? r : peer_up;
+    const int up = symtile::wrap_rank(r + p.shift(), p.world());
+    const int down = symtile::wrap_rank(r - p.shift() + p.world(), p.world());
+    src = (p.mode() == SYMTILE_GET) ? down : r;
+    dst = (p.mode() == SYMTILE_GET) ? r : up;
 }
 
 // Copy the nrows x nchunks block at (row0, chunk0) of the matrix from rank
-// src_rank to rank dst with the tile verb `copy`: both buffers are symmetric
-// objects named by their address in rank r's heap, and the verb translates
-// them.  With lg_w >= 0 a pass covers 1 << lg_w chunk columns of
-// kThreads >> lg_w rows, so a run of horizontally adjacent tiles streams
-// whole row segments (up to 8 KiB); lg_w < 0 (a tile width that is not a
-// power of two of chunks) numbers the chunks row-major through the block.
-template <int POLICY>
+// src_rank to rank dst: both buffers are symmetric objects named by their
+// address in rank r's heap and translated from there.  lg_w >= 0 is the tile
+// verb `copy`.  Rectangles whose width is no power of two are numbered
+// row-major, p.width chunks a row, so that no lane idles on a padded column;
+// loads of the next batch (LB chunks a thread) are issued before the stores of
+// this one (see symtile::move_tile).
+template <int POLICY, int LB>
 __device__ __forceinline__ void copy_block(const CopyParams& p, int r, int src_rank, int dst,
-                                           int row0, int chunk0, int nrows, int nchunks,
-                                           int lg_w) {
+                                           int row0, int chunk0, int nrows, int nchunks) {
     const uint8_t* src = reinterpret_cast<const uint8_t*>(p.bases[r] + p.src_off) +
                          (size_t)row0 * p.ld_bytes + (size_t)chunk0 * 16;
     uint8_t* dst_local = reinterpret_cast<uint8_t*>(p.bases[r] + p.dst_off) +
@@ -86,85 +99,134 @@ __device__ __forceinline__ void copy_block(const CopyParams& p, int r, int src_r
     g.rows = nrows;
     g.chunks = nchunks;
     g.ld_bytes = (uint32_t)p.ld_bytes;
-    g.lg_w = lg_w;
-    if (lg_w >= 0) {
+    g.lg_w = p.lg_w;
+    if (p.lg_w >= 0) {
         symtile::copy<POLICY, kBatch>(src, dst_local, g, src_rank, dst, r, p.bases, threadIdx.x,
                                       kThreads);
         return;
     }
     const symtile::rsrc_t rs = symtile::tile_rsrc(src, g, r, src_rank, p.bases);
     const symtile::rsrc_t rd = symtile::tile_rsrc(dst_local, g, r, dst, p.bases);
-    const int total = nrows * p.tile_chunks;
-    for (int base = threadIdx.x; base < total; base += kThreads * kBatch) {
-        u32x4 v[kBatch];
-        uint32_t off[kBatch];
+    const int total = nrows * p.width;
+    const int nb = (total + kThreads * LB - 1) / (kThreads * LB);
+    u32x4 x[LB], y[LB];
+    uint32_t ox[LB], oy[LB];
+    auto load = [&](u32x4 (&v)[LB], uint32_t (&off)[LB], int batch) {
 #pragma unroll
-        for (int u = 0; u < kBatch; ++u) {
-            const int q = base + u * kThreads;
-            const int row = q / p.tile_chunks, c = q - row * p.tile_chunks;
+        for (int u = 0; u < LB; ++u) {
+            const int q = (batch * LB + u) * kThreads + (int)threadIdx.x;
+            const int row = p.by_width(q), c = q - row * p.width;
             off[u] = (q < total && c < nchunks) ? (uint32_t)(row * p.ld_bytes + c * 16)
                                                 : symtile::kOOB;
             v[u] = symtile::buf_ld16(rs, off[u], 0);
         }
+    };
+    auto store = [&](const u32x4 (&v)[LB], const uint32_t (&off)[LB]) {
 #pragma unroll
-        for (int u = 0; u < kBatch; ++u) symtile::buf_st16p<POLICY>(v[u], rd, off[u], 0);
+        for (int u = 0; u < LB; ++u) symtile::buf_st16p<POLICY>(v[u], rd, off[u], 0);
+    };
+    load(x, ox, 0);
+    int i = 0;
+    for (; i + 2 < nb; i += 2) {
+        load(y, oy, i + 1);
+        store(x, ox);
+        load(x, ox, i + 2);
+        store(y, oy);
     }
-}
-
-// Copy tile `tile` of rank r (TC = 16-byte chunks per tile row when that is a
-// power of two dividing the thread count, else 0).
-template <int TC, int POLICY>
-__device__ __forceinline__ void copy_one_tile(const CopyParams& p, int r, int src_rank, int dst,
-                                              int tile) {
-    const int tr = tile / p.tiles_c, tc = tile - tr * p.tiles_c;
-    const int row0 = tr * p.tile_r;
-    const int chunk0 = tc * p.tile_chunks;
-    copy_block<POLICY>(p, r, src_rank, dst, row0, chunk0, min(p.tile_r, p.rows - row0),
-                       min(p.tile_chunks, p.row_chunks - chunk0),
-                       TC > 0 ? __builtin_ctz(TC) : -1);
-}
-
-template <int TC, int POLICY>
-__global__ __launch_bounds__(kThreads) void tile_copy_kernel(const CopyParams p) {
-    const int first = blockIdx.x * p.per_wg;
-    const int last = min(first + p.per_wg, p.nitems);
-    if (p.band_lg_w >= 0) {
-        // The run is per_wg adjacent tiles of one tile row: one rectangle.
-        const int r = p.only_rank >= 0 ? p.only_rank : first / p.ntiles;
-        int src, dst;
-        copy_ranks(p, r, src, dst);
-        const int t0 = first % p.ntiles;
-        const int tr = t0 / p.tiles_c, tc = t0 - tr * p.tiles_c;
-        const int row0 = tr * p.tile_r, chunk0 = tc * p.tile_chunks;
-        copy_block<POLICY>(p, r, src, dst, row0, chunk0, min(p.tile_r, p.rows - row0),
-                           min(p.per_wg * p.tile_chunks, p.row_chunks - chunk0), p.band_lg_w);
+    if (i + 1 < nb) {
+        load(y, oy, i + 1);
+        store(x, ox);
+        store(y, oy);
     } else {
-        for (int it = first; it < last; ++it) {
-            const int r = p.only_rank >= 0 ? p.only_rank : it / p.ntiles;
-            int src, dst;
-            copy_ranks(p, r, src, dst);
-            copy_one_tile<TC, POLICY>(p, r, src, dst, it % p.ntiles);
-        }
+        store(x, ox);
     }
-    // Publish: every tile of the run is in its destination heap before any
-    // of its counters moves.  Wave 0 releases once, then its lanes increment
-    // the run's counters together (one tile per lane), rather than one
-    // thread issuing them one after another into the same cache lines.
+}
+
+// Every tile of the run is in its destination heap before any of its
+// counters moves: the stores' acknowledgement is the release.  Wave 0's lanes
+// then increment the counters together (one tile per lane), rather than one
+// thread issuing them one after another into the same cache lines.
+template <typename F>
+__device__ __forceinline__ void publish_run(const CopyParams& p, int first, int last, F&& flag_of) {
     symtile::wg_stores_done();
     if (threadIdx.x < 64) {
-        if constexpr (POLICY == symtile::kStoreWriteThrough)
-            symtile::release_written_through();   // nothing of the run sits dirty in the L2
-        else
-            symtile::fence_release<__HIP_MEMORY_SCOPE_AGENT>();
+        symtile::release_written_through();
         for (int it = first + (int)threadIdx.x; it < last; it += 64) {
-            const int r = p.only_rank >= 0 ? p.only_rank : it / p.ntiles;
+            int r, tile;
+            flag_of(it, r, tile);
             int src, dst;
             copy_ranks(p, r, src, dst);
-            uint32_t* flag_local =
-                reinterpret_cast<uint32_t*>(p.bases[r] + p.flag_off) + it % p.ntiles;
+            uint32_t* flag_local = reinterpret_cast<uint32_t*>(p.bases[r] + p.flag_off) + tile;
             symtile::flag_signal(symtile::translate(flag_local, r, dst, p.bases));
         }
     }
+}
+
+// One rectangle per workgroup: run `seg` of tile row tr of rank r.
+__global__ __launch_bounds__(kThreads) void tile_copy_kernel(const CopyParams p) {
+    const int band = p.by_segs(blockIdx.x), seg = (int)blockIdx.x - band * p.segs;
+    const int rr = p.by_tiles_r(band), tr = band - rr * p.tiles_r;
+    const int r = p.only_rank() >= 0 ? p.only_rank() : rr;
+    const int t0 = seg * p.seg_tiles + min(seg, p.seg_more);
+    const int t1 = t0 + p.seg_tiles + (seg < p.seg_more ? 1 : 0);
+    int src, dst;
+    copy_ranks(p, r, src, dst);
+    const int row0 = tr * p.tile_r, chunk0 = t0 * p.tile_chunks;
+    copy_block<symtile::kStoreWriteThrough, kBatch>(
+        p, r, src, dst, row0, chunk0, min(p.tile_r, p.rows - row0),
+        min((t1 - t0) * p.tile_chunks, p.row_chunks - chunk0));
+    publish_run(p, t0, t1, [&](int it, int& rank, int& tile) {
+        rank = r;
+        tile = tr * p.tiles_c + it;
+    });
+}
+
+// A run of consecutive (rank, tile) items, tile by tile: the caller's
+// tiles_per_wg where it gives no rectangle.
+__global__ __launch_bounds__(kThreads) void tile_list_copy_kernel(const CopyParams p) {
+    const int first = blockIdx.x * p.per_wg;
+    const int last = min(first + p.per_wg, p.nitems);
+    auto item = [&](int it, int& r, int& tile) {
+        const int rr = p.by_ntiles(it);
+        r = p.only_rank() >= 0 ? p.only_rank() : rr;
+        tile = it - rr * p.ntiles;
+    };
+    for (int it = first; it < last; ++it) {
+        int r, tile, src, dst;
+        item(it, r, tile);
+        copy_ranks(p, r, src, dst);
+        const int tr = p.by_tiles_c(tile), tc = tile - tr * p.tiles_c;
+        const int row0 = tr * p.tile_r, chunk0 = tc * p.tile_chunks;
+        copy_block<symtile::kStoreWriteThrough, kBatch / 2>(p, r, src, dst, row0, chunk0,
+                                                min(p.tile_r, p.rows - row0),
+                                                min(p.tile_chunks, p.row_chunks - chunk0));
+    }
+    publish_run(p, first, last, item);
+}
+
+// Runs per tile row when the caller leaves it open.  A CU moves some 25 GB/s
+// each way whatever its workgroups do, so the busiest CU sets the time: the
+// count that gives it the fewest bytes, each run charged a fixed kRunBytes
+// for its latency (launch, first loads, acknowledgement), the smaller count
+// on a tie; one or two runs per CU are looked at, at most kThreads chunks
+// wide.  Runs need not be equal (19 tiles a row used to mean one tile per
+// workgroup: bf16 1500x1160, 4 ranks, 64x64 tiles 23.4 -> 6.5 us a call;
+// fp32 1442x684, 8 ranks, 128x128 tiles 14.9 -> 12.0).
+int choose_segs(size_t bands, int tiles_c, size_t tile_bytes, int tile_chunks, size_t cus) {
+    constexpr size_t kRunBytes = 32 << 10;
+    const size_t widest = std::max<size_t>(1, (size_t)kThreads / tile_chunks);
+    size_t best = 0, best_cost = SIZE_MAX;
+    for (size_t r = 1; r <= 2; ++r) {      // runs per CU (where the tile rows are fewer)
+        const size_t want = std::min<size_t>(std::max<size_t>(r * cus / bands, 1), tiles_c);
+        const size_t per = std::min((tiles_c + want - 1) / want, widest);
+        const size_t segs = (tiles_c + per - 1) / per;
+        const size_t cost = (bands * segs + cus - 1) / cus * (per * tile_bytes + kRunBytes);
+        if (cost < best_cost) {
+            best_cost = cost;
+            best = segs;
+        }
+    }
+    return (int)best;
 }
 
 }  // namespace
@@ -214,10 +276,9 @@ static symtile_status tile_copy_launch(symtile_heap* h, size_t src_off, size_t d
 
     CopyParams p;
     p.bases = h->dev_bases;
-    p.world = h->world;
-    p.shift = shift;
-    p.only_rank = only_rank;
-    p.mode = mode;
+    const int up = (shift % h->world + h->world) % h->world;
+    p.who = (uint32_t)h->world | (uint32_t)up << 4 | (uint32_t)(std::max(only_rank, -1) + 1) << 8 |
+            (uint32_t)mode << 12;
     p.src_off = src_off;
     p.dst_off = dst_off;
     p.flag_off = flag_off;
@@ -231,11 +292,9 @@ static symtile_status tile_copy_launch(symtile_heap* h, size_t src_off, size_t d
     const size_t nitems = ntiles * (only_rank >= 0 ? 1 : (size_t)h->world);
     if (nitems > INT32_MAX) return fail(SYMTILE_EINVAL, "too many tiles");
     p.nitems = (int)nitems;
-    if (tiles_per_wg == 0) {
-        // about one workgroup per CU: enough waves to fill the chip while
-        // keeping the number of L2 write-backs (one per workgroup) small;
-        // rounded to a power of two that divides the tiles of a tile row so
-        // that every run is one rectangle
+    const bool automatic = tiles_per_wg == 0;
+    if (automatic) {
+        // the equal power-of-two runs that the stride check below is stated for
         const size_t target = (size_t)std::max(1, symtile_host::cu_count(h->device));
         size_t per = std::max<size_t>(1, (nitems + target - 1) / target);
         size_t pow2 = 1;
@@ -245,38 +304,55 @@ static symtile_status tile_copy_launch(symtile_heap* h, size_t src_off, size_t d
     p.per_wg = tiles_per_wg;
     // Rectangle mode: runs never straddle a tile row and the run width
     // (rounded up to a power of two) fits the workgroup.
-    p.band_lg_w = -1;
+    int band_lg_w = -1;
     if (tiles_c % tiles_per_wg == 0) {
         const size_t width = (size_t)tiles_per_wg * p.tile_chunks;
         int lg = 0;
         while (((size_t)1 << lg) < width) ++lg;
-        if (((size_t)1 << lg) <= (size_t)kThreads) p.band_lg_w = lg;
+        if (((size_t)1 << lg) <= (size_t)kThreads) band_lg_w = lg;
     }
     // Buffer offsets are 32-bit: a tile's rows plus the out-of-range passes
     // that complete its last batch must stay below 2 GiB (the out-of-range
     // offset marker), or an offset could wrap back into the tile.
+    auto passes_fit = [&](size_t rows_per_pass) {
+        return ((size_t)tile_r + rows_per_pass * kBatch) * ld_bytes < (size_t(1) << 31);
+    };
     {
         size_t rows_per_pass = 0;
-        if (p.band_lg_w >= 0)
-            rows_per_pass = (size_t)kThreads >> p.band_lg_w;
+        if (band_lg_w >= 0)
+            rows_per_pass = (size_t)kThreads >> band_lg_w;
         else if (p.tile_chunks == 16 || p.tile_chunks == 32 || p.tile_chunks == 64)
             rows_per_pass = (size_t)kThreads / p.tile_chunks;
-        if (rows_per_pass &&
-            ((size_t)tile_r + rows_per_pass * kBatch) * ld_bytes >= (size_t(1) << 31))
+        if (rows_per_pass && !passes_fit(rows_per_pass))
             return fail(SYMTILE_EINVAL, "row stride too large for this tile shape");
     }
+    p.tiles_r = tiles_r;
+    const size_t bands = (size_t)tiles_r * (only_rank >= 0 ? 1 : (size_t)h->world);
+    p.segs = automatic ? choose_segs(bands, tiles_c, (size_t)tile_r * tile_c * esize, p.tile_chunks,
+                                     (size_t)std::max(1, symtile_host::cu_count(h->device)))
+             : band_lg_w >= 0 ? tiles_c / tiles_per_wg
+                              : 0;
+    const int run_tiles = p.segs ? (tiles_c + p.segs - 1) / p.segs : 1;
+    p.seg_tiles = p.segs ? tiles_c / p.segs : 0;
+    p.seg_more = p.segs ? tiles_c % p.segs : 0;
+    p.width = run_tiles * p.tile_chunks;
+    p.lg_w = -1;
+    if ((p.width & (p.width - 1)) == 0 && p.width <= kThreads) {
+        const int lg = __builtin_ctz(p.width);
+        if (passes_fit((size_t)kThreads >> lg)) p.lg_w = lg;
+    }
+    p.by_segs = make_div(std::max(p.segs, 1));
+    p.by_tiles_r = make_div(tiles_r);
+    p.by_ntiles = make_div(p.ntiles);
+    p.by_tiles_c = make_div(tiles_c);
+    p.by_width = make_div(p.width);
 
     int prev = -1;
     if (symtile_status st = symtile_host::set_device(h, &prev)) return st;
-    const dim3 grid((unsigned)((nitems + p.per_wg - 1) / p.per_wg));
+    const dim3 grid((unsigned)(p.segs ? bands * p.segs : (nitems + p.per_wg - 1) / p.per_wg));
     hipStream_t stream = static_cast<hipStream_t>(s);
-    const void* kernel;
-    switch (p.tile_chunks) {
-        case 16: kernel = reinterpret_cast<const void*>(&tile_copy_kernel<16, symtile::kStoreWriteThrough>); break;
-        case 32: kernel = reinterpret_cast<const void*>(&tile_copy_kernel<32, symtile::kStoreWriteThrough>); break;
-        case 64: kernel = reinterpret_cast<const void*>(&tile_copy_kernel<64, symtile::kStoreWriteThrough>); break;
-        default: kernel = reinterpret_cast<const void*>(&tile_copy_kernel<0, symtile::kStoreWriteThrough>); break;
-    }
+    const void* kernel = p.segs ? reinterpret_cast<const void*>(&tile_copy_kernel)
+                                : reinterpret_cast<const void*>(&tile_list_copy_kernel);
     void* args[] = {&p};
     hipError_t e = t0 ? hipExtLaunchKernel(kernel, grid, dim3(kThreads), args, 0, stream, t0, t1, 0)
                       : hipLaunchKernel(kernel, grid, dim3(kThreads), args, 0, stream);

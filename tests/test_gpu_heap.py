@@ -537,3 +537,41 @@ def test_litmus_rejects_bad_arguments():
             pkg.symtile_litmus_sb(heap.handle, *args, 0, res.data_ptr(), pkg.current_stream())
         assert e.value.name == name, args
     heap.barrier()
+
+
+@pytest.mark.parametrize("mode", [0, 1], ids=["put", "get"])
+@pytest.mark.parametrize("case", [
+    # world, rows, cols, tile_r, tile_c, dtype: odd counts of tiles a row, runs of
+    # unequal length, widths that are no power of two, one tile row, wide tiles
+    (4, 300, 1160, 64, 64, "bf16"), (2, 130, 2040, 64, 24, "f16"), (8, 33, 260, 32, 4, "f32"),
+    (3, 64, 8, 64, 8, "bf16"), (1, 70, 1000, 7, 40, "f32"), (2, 20, 16384, 16, 16384, "f32"),
+    (2, 9, 12304, 8, 4104, "bf16"), (8, 520, 2048, 128, 128, "f32"),
+], ids=lambda c: "w%d_%dx%d_t%dx%d_%s" % c)
+def test_heap_tile_copy_automatic_runs(case, mode):
+    """The library's own split of the tile rows into runs, and the caller's (one,
+    three and all tiles of a row per workgroup), for all ranks and one, with shifts
+    of either sign: every byte and counter as the oracle's copy leaves them."""
+    pkg = sym()
+    world, rows, cols, tr, tc, dt = case
+    tdt = {"bf16": torch.bfloat16, "f16": torch.float16, "f32": torch.float32}[dt]
+    code = {"bf16": pkg.BF16, "f16": pkg.F16, "f32": pkg.F32}[dt]
+    ival = torch.int16 if dt != "f32" else torch.int32
+    heap, src, dst, flags = _copy_heap(pkg, world, rows, cols, tdt)
+    g = torch.Generator().manual_seed(5)
+    send = torch.randint(-2 ** 15, 2 ** 15, (world, rows, cols), generator=g).to(ival)
+    heap.slots_view(src, (rows, cols), ival).copy_(send.cuda())
+    tiles_c = -(-cols // tc)
+    ntiles = -(-rows // tr) * tiles_c
+    for only, shift, per in ((-1, 1, 0), (world - 1, -1, 0), (-1, -world - 2, 1), (-1, 2, 3),
+                             (0, 1, tiles_c)):
+        heap.slots_view(flags, (ntiles,), torch.int32).zero_()
+        heap.slots_view(dst, (rows, cols), ival).zero_()
+        pkg.symtile_tile_copy(heap.handle, src, dst, rows, cols, cols, code, tr, tc, shift, only,
+                              flags, tiles_per_wg=per, stream=pkg.current_stream(), mode=mode)
+        heap.barrier()
+        recv = heap.slots_view(dst, (rows, cols), ival).cpu().numpy()
+        fl = heap.slots_view(flags, (ntiles,), torch.int32).cpu().numpy()
+        want, wf = oracle.tile_copy(send.numpy(), np.zeros_like(send.numpy()), tr, tc, shift,
+                                    only_rank=only, get=bool(mode))
+        assert np.array_equal(recv, want), (only, shift, per)
+        assert np.array_equal(fl, wf.astype(np.int32)), (only, shift, per)
