@@ -115,8 +115,9 @@ enum : int { kStoreDefault = 0, kStoreNonTemporal = 2, kStoreWriteThrough = 17,
 // Load cache policies: kLoadDefault may hit a line this XCD's L2 holds from
 // before; kLoadCoherent (sc0 sc1, the encoding the memory model gives a
 // system-scope relaxed atomic load) reads the value that is coherent for
-// every XCD, not a copy the L2 kept.
-enum : int { kLoadDefault = 0, kLoadCoherent = 17 };
+// every XCD, not a copy the L2 kept; kLoadStream (nt) marks lines that are
+// read once, so that they do not push others out of the caches.
+enum : int { kLoadDefault = 0, kLoadStream = 2, kLoadCoherent = 17 };
 
 template <int POLICY>
 __device__ __forceinline__ u32x4 buf_ld16p(rsrc_t r, uint32_t voff, uint32_t soff) {
@@ -410,7 +411,7 @@ __device__ __forceinline__ rsrc_t tile_rsrc(const void* p, const TileGeom& g, in
 // wait before storing batch i leaves the newer loads and stores in flight.
 // Passes past the last one lie outside the resources (zero loads, dropped
 // stores).  The loop body has no branch, so the compiler's waits stay exact.
-template <int POLICY, int BATCH>
+template <int POLICY, int BATCH, int LOAD = kLoadDefault>
 __device__ __forceinline__ void move_tile(rsrc_t rs, rsrc_t rd, const TileLanes& L) {
     const int nb = (L.passes + BATCH - 1) / BATCH;
     if (nb <= 0) return;
@@ -418,7 +419,7 @@ __device__ __forceinline__ void move_tile(rsrc_t rs, rsrc_t rd, const TileLanes&
     auto load = [&](u32x4 (&v)[BATCH], int batch) {
 #pragma unroll
         for (int u = 0; u < BATCH; ++u)
-            v[u] = buf_ld16(rs, L.voff, (uint32_t)(batch * BATCH + u) * L.pass_bytes);
+            v[u] = buf_ld16p<LOAD>(rs, L.voff, (uint32_t)(batch * BATCH + u) * L.pass_bytes);
     };
     auto store = [&](const u32x4 (&v)[BATCH], int batch) {
 #pragma unroll
@@ -446,12 +447,13 @@ __device__ __forceinline__ void move_tile(rsrc_t rs, rsrc_t rd, const TileLanes&
 // as it lies in to_rank's heap (both addresses named in cur's heap).  Every
 // thread of the workgroup (threads of them) calls it; it returns when this
 // thread's stores are issued, not acknowledged (see wg_stores_done).
-template <int POLICY = kStoreDefault, int BATCH = 8>
+template <int POLICY = kStoreDefault, int BATCH = 8, int LOAD = kLoadDefault>
 __device__ __forceinline__ void copy(const void* src, void* dst, const TileGeom& g, int from_rank,
                                      int to_rank, int cur, const uint64_t* __restrict__ bases,
                                      int tid, int threads) {
-    move_tile<POLICY, BATCH>(tile_rsrc(src, g, cur, from_rank, bases),
-                             tile_rsrc(dst, g, cur, to_rank, bases), tile_lanes(g, tid, threads));
+    move_tile<POLICY, BATCH, LOAD>(tile_rsrc(src, g, cur, from_rank, bases),
+                                   tile_rsrc(dst, g, cur, to_rank, bases),
+                                   tile_lanes(g, tid, threads));
 }
 
 // put: from the executing rank's own heap to `remote`'s (the write is remote).

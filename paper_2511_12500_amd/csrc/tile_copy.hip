@@ -12,7 +12,9 @@
 // issuing a batch of loads before the matching stores so many requests are
 // in flight per wave.  Stores are written through to memory (cold copies
 // measured fastest that way), so their acknowledgement is the release and the
-// run's counters follow it.
+// run's counters follow it.  Loads carry the streaming hint (kLoadStream) when
+// source and destination together fill the 256 MiB memory-side cache, so that
+// the next call could not find its source there anyway (see kStreamBytes).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -88,7 +90,7 @@ __device__ __forceinline__ void copy_ranks(const CopyParams& p, int r, int& src,
 // row-major, p.width chunks a row, so that no lane idles on a padded column;
 // loads of the next batch (LB chunks a thread) are issued before the stores of
 // this one (see symtile::move_tile).
-template <int POLICY, int LB>
+template <int POLICY, int LB, int LOAD>
 __device__ __forceinline__ void copy_block(const CopyParams& p, int r, int src_rank, int dst,
                                            int row0, int chunk0, int nrows, int nchunks) {
     const uint8_t* src = reinterpret_cast<const uint8_t*>(p.bases[r] + p.src_off) +
@@ -101,8 +103,8 @@ __device__ __forceinline__ void copy_block(const CopyParams& p, int r, int src_r
     g.ld_bytes = (uint32_t)p.ld_bytes;
     g.lg_w = p.lg_w;
     if (p.lg_w >= 0) {
-        symtile::copy<POLICY, kBatch>(src, dst_local, g, src_rank, dst, r, p.bases, threadIdx.x,
-                                      kThreads);
+        symtile::copy<POLICY, kBatch, LOAD>(src, dst_local, g, src_rank, dst, r, p.bases,
+                                            threadIdx.x, kThreads);
         return;
     }
     const symtile::rsrc_t rs = symtile::tile_rsrc(src, g, r, src_rank, p.bases);
@@ -118,7 +120,7 @@ __device__ __forceinline__ void copy_block(const CopyParams& p, int r, int src_r
             const int row = p.by_width(q), c = q - row * p.width;
             off[u] = (q < total && c < nchunks) ? (uint32_t)(row * p.ld_bytes + c * 16)
                                                 : symtile::kOOB;
-            v[u] = symtile::buf_ld16(rs, off[u], 0);
+            v[u] = symtile::buf_ld16p<LOAD>(rs, off[u], 0);
         }
     };
     auto store = [&](const u32x4 (&v)[LB], const uint32_t (&off)[LB]) {
@@ -163,6 +165,7 @@ __device__ __forceinline__ void publish_run(const CopyParams& p, int first, int 
 }
 
 // One rectangle per workgroup: run `seg` of tile row tr of rank r.
+template <int LOAD>
 __global__ __launch_bounds__(kThreads) void tile_copy_kernel(const CopyParams p) {
     const int band = p.by_segs(blockIdx.x), seg = (int)blockIdx.x - band * p.segs;
     const int rr = p.by_tiles_r(band), tr = band - rr * p.tiles_r;
@@ -172,7 +175,7 @@ __global__ __launch_bounds__(kThreads) void tile_copy_kernel(const CopyParams p)
     int src, dst;
     copy_ranks(p, r, src, dst);
     const int row0 = tr * p.tile_r, chunk0 = t0 * p.tile_chunks;
-    copy_block<symtile::kStoreWriteThrough, kBatch>(
+    copy_block<symtile::kStoreWriteThrough, kBatch, LOAD>(
         p, r, src, dst, row0, chunk0, min(p.tile_r, p.rows - row0),
         min((t1 - t0) * p.tile_chunks, p.row_chunks - chunk0));
     publish_run(p, t0, t1, [&](int it, int& rank, int& tile) {
@@ -197,12 +200,19 @@ __global__ __launch_bounds__(kThreads) void tile_list_copy_kernel(const CopyPara
         copy_ranks(p, r, src, dst);
         const int tr = p.by_tiles_c(tile), tc = tile - tr * p.tiles_c;
         const int row0 = tr * p.tile_r, chunk0 = tc * p.tile_chunks;
-        copy_block<symtile::kStoreWriteThrough, kBatch / 2>(p, r, src, dst, row0, chunk0,
+        copy_block<symtile::kStoreWriteThrough, kBatch / 2, symtile::kLoadDefault>(p, r, src, dst, row0, chunk0,
                                                 min(p.tile_r, p.rows - row0),
                                                 min(p.tile_chunks, p.row_chunks - chunk0));
     }
     publish_run(p, first, last, item);
 }
+
+// Bytes read and written by a call from which its loads are streaming ones.
+// fp32, 8 ranks, us a call without / with the hint, the same buffers again and
+// again: 128 MiB 20.0 / 21.2, 224 MiB 38.2 / 38.5, 244 MiB 39.9 / 41.8, 256 MiB
+// 44.6 / 39.9; three sets of buffers in turn: 256 MiB 48.1 / 47.0.  (On the
+// stores too it costs more than it gives: 11.8 -> 15.6 on 1442x684.)
+constexpr size_t kStreamBytes = size_t(256) << 20;
 
 // Runs per tile row when the caller leaves it open.  A CU moves some 25 GB/s
 // each way whatever its workgroups do, so the busiest CU sets the time: the
@@ -351,8 +361,11 @@ static symtile_status tile_copy_launch(symtile_heap* h, size_t src_off, size_t d
     if (symtile_status st = symtile_host::set_device(h, &prev)) return st;
     const dim3 grid((unsigned)(p.segs ? bands * p.segs : (nitems + p.per_wg - 1) / p.per_wg));
     hipStream_t stream = static_cast<hipStream_t>(s);
-    const void* kernel = p.segs ? reinterpret_cast<const void*>(&tile_copy_kernel)
-                                : reinterpret_cast<const void*>(&tile_list_copy_kernel);
+    const bool stream_loads = 2 * (size_t)rows * cols * esize * (bands / tiles_r) >= kStreamBytes;
+    const void* kernel =
+        !p.segs        ? reinterpret_cast<const void*>(&tile_list_copy_kernel)
+        : stream_loads ? reinterpret_cast<const void*>(&tile_copy_kernel<symtile::kLoadStream>)
+                       : reinterpret_cast<const void*>(&tile_copy_kernel<symtile::kLoadDefault>);
     void* args[] = {&p};
     hipError_t e = t0 ? hipExtLaunchKernel(kernel, grid, dim3(kThreads), args, 0, stream, t0, t1, 0)
                       : hipLaunchKernel(kernel, grid, dim3(kThreads), args, 0, stream);
