@@ -110,14 +110,14 @@ struct GasCall {
     // consumers put the others.
     int direct_last, direct_mid;
     // by gemm_wgs, split, the tiles of a full swizzle group, the tile rows of
-    // a full and of the last group, and tiles_n (see set_divs)
-    Div by_wgs, by_split, by_width, by_rows, by_last_rows, by_tiles_n;
+    // a full and of the last group, tiles_n and num_tiles (see set_divs)
+    Div by_wgs, by_split, by_width, by_rows, by_last_rows, by_tiles_n, by_tiles;
     // ROLE_REDUCE: bands of rows per tile (units = tiles * reduce_bands), and
     // whether the tile goes to every slot (fused) or the local one (bulk).
     int reduce_bands, reduce_all;
 };
 
-// A call as the kernels take it: 160 bytes, ordered so that what a workgroup
+// A call as the kernels take it: 168 bytes, ordered so that what a workgroup
 // needs before its first loads lies in the first 128.  Kernel arguments are in
 // host memory, and each 64-byte line of them that a workgroup touches is a
 // round trip there (back-to-back calls, us, with the 232 bytes of GasCall ->
@@ -134,7 +134,7 @@ struct GasParams {
     uint32_t shifts;        // of by_wgs, by_width, by_rows, by_last_rows
     uint32_t mul_last_rows, mul_split;
     uint32_t share;         // direct_last, direct_mid, reduce_all: 4 bits each; reduce_bands: 8
-    uint32_t shifts2;       // of by_split, by_tiles_n
+    uint32_t shifts2;       // of by_split, by_tiles_n, by_tiles
     uint16_t* C;
     uint32_t* arrived;
     const uint64_t* bases;
@@ -145,9 +145,9 @@ struct GasParams {
     uint32_t* ready;
     uint32_t epoch, spin_limit;
     int copy_wgs;
-    uint32_t mul_tiles_n;
+    uint32_t mul_tiles_n, mul_tiles, reserved;
 };
-static_assert(sizeof(GasParams) == 160, "kernel arguments");
+static_assert(sizeof(GasParams) == 168, "kernel arguments");
 
 GasParams pack(const GasCall& c) {
     GasParams a{};
@@ -156,11 +156,11 @@ GasParams pack(const GasCall& c) {
     a.tiles_m = c.tiles_m, a.tiles_n = c.tiles_n, a.gemm_wgs = c.gemm_wgs, a.group_m = c.group_m;
     a.mul_wgs = c.by_wgs.mul, a.mul_width = c.by_width.mul, a.mul_rows = c.by_rows.mul;
     a.mul_last_rows = c.by_last_rows.mul, a.mul_split = c.by_split.mul;
-    a.mul_tiles_n = c.by_tiles_n.mul;
+    a.mul_tiles_n = c.by_tiles_n.mul, a.mul_tiles = c.by_tiles.mul;
     a.who = (uint32_t)c.rank | (uint32_t)c.world << 4 | (uint32_t)c.role << 8 |
             (uint32_t)c.nontemporal << 12 | (uint32_t)c.sk_band << 16 | (uint32_t)c.split << 20;
     a.shifts = c.by_wgs.sh | c.by_width.sh << 8 | c.by_rows.sh << 16 | c.by_last_rows.sh << 24;
-    a.shifts2 = c.by_split.sh | c.by_tiles_n.sh << 8;
+    a.shifts2 = c.by_split.sh | c.by_tiles_n.sh << 8 | c.by_tiles.sh << 16;
     a.share = (uint32_t)c.direct_last | (uint32_t)c.direct_mid << 4 |
               (uint32_t)c.reduce_all << 8 | (uint32_t)c.reduce_bands << 12;
     a.arrived = c.arrived, a.bases = c.bases, a.trace = c.trace, a.sk_cnt = c.sk_cnt;
@@ -189,6 +189,7 @@ __device__ __forceinline__ GasCall unpack(const GasParams& a) {
     c.by_last_rows = Div{a.mul_last_rows, a.shifts >> 24};
     c.by_split = Div{a.mul_split, a.shifts2 & 255};
     c.by_tiles_n = Div{a.mul_tiles_n, a.shifts2 >> 8 & 255};
+    c.by_tiles = Div{a.mul_tiles, a.shifts2 >> 16 & 255};
     c.arrived = a.arrived, c.bases = a.bases, c.trace = a.trace, c.sk_cnt = a.sk_cnt;
     c.err = a.err, c.ready = a.ready, c.epoch = a.epoch, c.spin_limit = a.spin_limit;
     c.copy_wgs = a.copy_wgs;
@@ -271,7 +272,11 @@ __device__ __forceinline__ int swz_b(int k) {
 // Producer-order work unit u -> (tile row, tile column, K slice).  The XCD
 // remap makes consecutive units land on one XCD, and the slices of a tile are
 // consecutive units, so with split-K they share that XCD's L2 (and the
-// partial tiles they exchange stay there).  Without split-K a unit is a tile.
+// partial tiles they exchange stay there).  Where the slices exchange nothing
+// (the reduction-kernel mode) consecutive units are the tiles of one slice
+// instead, so that an XCD reads a part of K of all its panels (128x128 tiles, 1024x4096x1024 in 4 slices: 3 MiB of A and
+// B per XCD, which its L2 holds, instead of 6; 26.9 -> 25.0 us a call; 64x8192x3584
+// 22.2 -> 21.4).  Without split-K a unit is a tile.
 __device__ __forceinline__ void unit_coords(int u, int G, const GasCall& p, int& tm, int& tn,
                                             int& s) {
     int L = u;
@@ -281,9 +286,14 @@ __device__ __forceinline__ void unit_coords(int u, int G, const GasCall& p, int&
         L = round * G + (pos & 7) * (G >> 3) + (pos >> 3);
     }
     if (p.split > 1) {
-        const int q = p.by_split(L);
-        s = L - q * p.split;
-        L = q;
+        if (p.sk_band == 2) {
+            s = p.by_tiles(L);
+            L -= s * p.num_tiles;
+        } else {
+            const int q = p.by_split(L);
+            s = L - q * p.split;
+            L = q;
+        }
     } else {
         s = 0;
     }
@@ -1991,6 +2001,7 @@ void set_divs(GasCall& p) {
     p.by_rows = make_div(p.group_m);
     p.by_last_rows = make_div(p.tiles_m % p.group_m ? p.tiles_m % p.group_m : p.group_m);
     p.by_tiles_n = make_div(p.tiles_n);
+    p.by_tiles = make_div(p.num_tiles);
 }
 
 // Split-K workspace: two counters per tile, rounded up to 256 bytes, then
