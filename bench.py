@@ -285,21 +285,22 @@ def gas_leg(args, torch, sym, case, variant, split_k, gemm_wgs, copy_wgs, steps,
                          "kernel": "gas_kernel<%d,%d,%s,%d waves>" % (
                              case.tm, case.tn, wl.dtype,
                              waves_used("%dx%d" % (case.tm, case.tn), variant, split_k,
-                                        kw["waves_per_wg"])),
+                                        kw["waves_per_wg"], wl.K)),
                          "algorithmic_flops_per_launch": wl.flops,
                          "algorithmic_bytes_per_launch": gemm_bytes(wl),
                          "avg_launch_ms": ms}}
 
 
-def waves_used(tile: str, variant: str, split_k: int, waves: int) -> int:
+def waves_used(tile: str, variant: str, split_k: int, waves: int, K: int) -> int:
     """Waves per producer workgroup the library runs for these arguments
     (waves 0 = the library's default for the tile and schedule)."""
+    if tile == "64x64":
+        return 4 if K <= 256 and split_k <= 1 else 8
+    if tile != "256x256":
+        return 8
     if waves:
         return waves
-    if tile == "64x64" or (tile == "256x256" and split_k <= 1 and
-                           variant in ("fused_seq", "bulk_sync")):
-        return 4
-    return 8
+    return 4 if split_k <= 1 and variant in ("fused_seq", "bulk_sync") else 8
 
 
 def gemm_bytes(wl) -> int:

@@ -48,8 +48,7 @@ struct Div {
 };
 
 inline Div make_div(int d) {
-    uint32_t sh = 0;
-    while ((uint64_t(1) << sh) < (uint64_t)d) ++sh;
+    const uint32_t sh = d > 1 ? 32 - __builtin_clz((uint32_t)d - 1) : 0;
     return Div{(uint32_t)(((uint64_t(1) << (31 + sh)) + d - 1) / d), sh};
 }
 

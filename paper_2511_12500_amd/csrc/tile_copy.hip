@@ -284,7 +284,7 @@ static symtile_status tile_copy_launch(symtile_heap* h, size_t src_off, size_t d
         (flag_off < dst_off + span && dst_off < flag_off + ntiles * 4))
         return fail(SYMTILE_EINVAL, "flags overlap the data");
 
-    CopyParams p;
+    CopyParams p{};
     p.bases = h->dev_bases;
     const int up = (shift % h->world + h->world) % h->world;
     p.who = (uint32_t)h->world | (uint32_t)up << 4 | (uint32_t)(std::max(only_rank, -1) + 1) << 8 |
@@ -351,11 +351,14 @@ static symtile_status tile_copy_launch(symtile_heap* h, size_t src_off, size_t d
         const int lg = __builtin_ctz(p.width);
         if (passes_fit((size_t)kThreads >> lg)) p.lg_w = lg;
     }
-    p.by_segs = make_div(std::max(p.segs, 1));
-    p.by_tiles_r = make_div(tiles_r);
-    p.by_ntiles = make_div(p.ntiles);
-    p.by_tiles_c = make_div(tiles_c);
-    p.by_width = make_div(p.width);
+    if (p.segs) {
+        p.by_segs = make_div(p.segs);
+        p.by_tiles_r = make_div(tiles_r);
+    } else {
+        p.by_ntiles = make_div(p.ntiles);
+        p.by_tiles_c = make_div(tiles_c);
+    }
+    if (p.lg_w < 0) p.by_width = make_div(p.width);
 
     int prev = -1;
     if (symtile_status st = symtile_host::set_device(h, &prev)) return st;

@@ -1031,3 +1031,20 @@ def test_tile_mapping_covers_every_tile_once(case, K):
         p.run(0, FUSED, group_m=gm, split_k=split)
         p.barrier()
         check_gathered(p, want)
+
+
+def test_banded_64x64_grid_larger_than_resident():
+    """A banded call with more work units than resident workgroups (64 x 64 tiles,
+    up to four per CU are accepted) sums with the reduction kernel: same bits."""
+    world, M, N, K = 2, 64 * 20, 64 * 10, 520
+    p = Problem(world, M, N, K, "bf16", 64, 64, seed=8)
+    want = {0: oracle_block_bounded(p.A, p.shards[0], "bf16")}
+    heaps = []
+    for mode, g in ((1, 0), (2, 400)):
+        p.sentinel()
+        p.run(0, FUSED, split_k=2, split_reduce=mode, gemm_wgs=g)
+        p.barrier()
+        check_gathered(p, want)
+        heaps.append(u16(p.out.C_all()).copy())
+        assert np.all(_ws_counters(p) == 0)
+    assert np.array_equal(heaps[0], heaps[1])
