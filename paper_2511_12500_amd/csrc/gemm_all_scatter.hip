@@ -1832,8 +1832,14 @@ __global__ __launch_bounds__(copy_threads<BM>()) void scatter_kernel(const GasPa
 
 // Copy kernel of the unfused producer-consumer schedule (Section 4.1.2):
 // runs on its own stream next to the producer grid of gas_kernel.
+// Its register allocation (waves_per_eu) takes a CU: beside a producer's
+// workgroup it finds no room, so the two grids share the CUs out as their sizes
+// say.  Without, the dispatcher puts consumers on the producers' CUs and leaves
+// others idle.
 template <int BM, int BN>
-__global__ __launch_bounds__(copy_threads<BM>()) void consumer_kernel(const GasParams a) {
+__global__ __launch_bounds__(copy_threads<BM>())
+__attribute__((amdgpu_waves_per_eu(copy_threads<BM>() / 256, copy_threads<BM>() / 256)))
+void consumer_kernel(const GasParams a) {
     consume_tiles<BM, BN, copy_threads<BM>()>(unpack(a), blockIdx.x, gridDim.x);
 }
 

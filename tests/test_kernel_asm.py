@@ -110,3 +110,39 @@ def test_k_loop_has_no_spills_copies_or_drains(asm, dtype):
     assert not [w for w in waits if re.search(r"vmcnt\(0\)", w)]
     # every staging register goes to LDS only after its own load: exact waits
     assert any(re.search(r"vmcnt\((1[0-9]|[1-9])\)", w) for w in waits)
+
+
+# ---------------------------------------------------------------- two grids side by side
+
+def kernel_registers(lines, pattern):
+    """{kernel: (vector registers per wave as allocated, workgroup size)} of the kernels
+    whose mangled name matches."""
+    text = "\n".join(lines)
+    out = {}
+    for name, body in re.findall(r"\.amdhsa_kernel (\S+)\n(.*?)\.end_amdhsa_kernel", text, re.S):
+        if re.search(pattern, name):
+            vgprs = int(re.search(r"\.amdhsa_next_free_vgpr (\d+)", body).group(1))
+            meta = text[text.index(".amdgpu_metadata"):]
+            meta = meta[:meta.index(f".symbol:         {name}.kd")]
+            wg = int(re.findall(r"\.max_flat_workgroup_size: (\d+)", meta)[-1])
+            out[name] = (-(-vgprs // 8) * 8, wg)
+    return out
+
+
+@pytest.mark.parametrize("tile", [(64, 64), (128, 128), (256, 128), (256, 256), (256, 224)],
+                         ids="%dx%d".__mod__)
+def test_copy_kernel_shares_no_cu_with_a_producer(asm, tile):
+    """UNFUSED_PC starts a grid of producers and one of consumers, sized to
+    share the CUs out between them: a SIMD's 512 vector registers must not hold
+    the waves of one workgroup of each, nor those of two consumers."""
+    prod = kernel_registers(asm, r"gas_pc_kernelILi%dELi%dE" % tile)
+    cons = kernel_registers(asm, r"consumer_kernelILi%dELi%dE" % tile)
+    assert prod and len(cons) == 1
+
+    def per_simd(regs, wg):
+        return regs * (wg // 64 // 4)
+
+    c = per_simd(*next(iter(cons.values())))
+    assert c <= 512 < 2 * c
+    for name, r in prod.items():
+        assert per_simd(*r) <= 512 < per_simd(*r) + c, name
