@@ -42,7 +42,6 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <map>
 #include <mutex>
 #include <string>
 #include <type_traits>
@@ -1943,33 +1942,16 @@ const Variant* find_wave_spec_variant(int bm, int bn, bool bf16) {
     return nullptr;
 }
 
-// *resident: workgroups of the kernel that can be resident at once.  *limit:
-// the largest grid a schedule with waiting workgroups accepts.  They differ
-// for 64 x 64 tiles, whose deep LDS ring leaves room for one workgroup per CU
-// where its 32 KiB predecessor left room for four: larger grids are accepted
-// as before and run as a resident grid that takes more tiles per workgroup.
-symtile_status coresident_limit(const Variant* v, const void* kernel, int device, int* cus,
-                                int* limit, int* resident) {
-    int n_cu = symtile_host::cu_count(device);
-    if (n_cu <= 0) return symtile_host::fail(SYMTILE_EHIP, "cannot read the CU count");
-    // workgroups of a kernel per CU: fixed for the process, so asked once per
-    // (kernel, device) (the query costs microseconds on every call's path)
-    static std::mutex mu;
-    static std::map<std::pair<const void*, int>, int> per_cu_known;
-    int per_cu = 0;
-    {
-        std::lock_guard<std::mutex> lock(mu);
-        auto it = per_cu_known.find({kernel, device});
-        if (it != per_cu_known.end()) per_cu = it->second;
-    }
-    if (per_cu == 0) {
-        SYMTILE_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, 64 * v->waves, 0));
-        std::lock_guard<std::mutex> lock(mu);
-        per_cu_known[{kernel, device}] = per_cu;
-    }
-    *cus = n_cu;
-    *resident = per_cu * n_cu;
-    *limit = (v->bm == 64 ? std::max(per_cu, 4) : per_cu) * n_cu;
+// *cus: compute units, each of which holds one workgroup (the register
+// allocation that amdgpu_waves_per_eu gives a kernel leaves no room for a
+// second), so a grid whose workgroups wait for each other has at most that
+// many.  *limit: the largest grid a schedule with waiting workgroups accepts.
+// They differ for 64 x 64 tiles: larger grids run as a grid of *cus workgroups
+// that take more tiles each.
+symtile_status coresident_limit(const Variant* v, int device, int* cus, int* limit) {
+    *cus = symtile_host::cu_count(device);
+    if (*cus <= 0) return symtile_host::fail(SYMTILE_EHIP, "cannot read the CU count");
+    *limit = (v->bm == 64 ? 4 : 1) * *cus;
     return SYMTILE_OK;
 }
 
@@ -2075,8 +2057,8 @@ extern "C" symtile_status symtile_device_info(int device, int tile_m, int tile_n
     if (tile_m == 0 && tile_n == 0) tile_m = tile_n = 256;
     const Variant* v = find_variant(tile_m, tile_n, true, 0);
     if (!v) return symtile_host::fail(SYMTILE_EUNSUPPORTED, "tile shape not built");
-    int cus = 0, lim = 0, resident = 0;
-    if (symtile_status st = coresident_limit(v, v->gas_pc, device, &cus, &lim, &resident)) return st;
+    int cus = 0, lim = 0;
+    if (symtile_status st = coresident_limit(v, device, &cus, &lim)) return st;
     if (cu_count) *cu_count = cus;
     if (max_coresident_wgs) *max_coresident_wgs = lim;
     return SYMTILE_OK;
@@ -2183,10 +2165,8 @@ extern "C" symtile_status symtile_gemm_all_scatter(
         }
     }
 
-    int cus = 0, limit = 0, resident = 0;
-    if (symtile_status st =
-            coresident_limit(v, pc ? v->gas_pc : v->gas, h->device, &cus, &limit, &resident))
-        return st;
+    int cus = 0, limit = 0;
+    if (symtile_status st = coresident_limit(v, h->device, &cus, &limit)) return st;
 
     GasCall p;
     p.A = static_cast<const uint16_t*>(A);
@@ -2268,7 +2248,7 @@ extern "C" symtile_status symtile_gemm_all_scatter(
             p.sk_band = cfg.split_reduce == SYMTILE_SPLIT_REDUCE_BANDED ||
                         (automatic && fits && split == 2);
             if (cfg.split_reduce == SYMTILE_SPLIT_REDUCE_KERNEL || (automatic && split > 2) ||
-                (p.sk_band == 1 && g > resident))
+                (p.sk_band == 1 && g > cus))
                 p.sk_band = 2;
         }
         p.role = cfg.variant == SYMTILE_FUSED_SEQ ? ROLE_FUSED : ROLE_LOCAL_ONLY;
@@ -2369,9 +2349,9 @@ extern "C" symtile_status symtile_gemm_all_scatter(
         return fail(SYMTILE_EUNSUPPORTED,
                     "gemm_wgs + copy_wgs = " + std::to_string(g + c) +
                         " exceeds the co-resident limit " + std::to_string(limit));
-    if (g + c > resident) {                      // the same split of a resident grid
-        c = std::max(1, (int)((int64_t)c * resident / (g + c)));
-        g = resident - c;
+    if (g + c > cus) {                           // a resident grid instead
+        c = std::min(c, std::max(1, cus / 4));
+        g = cus - c;
     }
     if (world_size == 1) c = std::min(c, ntiles);
     p.gemm_wgs = g;

@@ -954,21 +954,28 @@ def test_deep_stage_edges_match_oracle(tile, K):
         assert all(np.array_equal(h, heaps[0]) for h in heaps)
 
 
-def test_wg_spec_64x64_grid_larger_than_resident():
+@pytest.mark.parametrize("K", [136, 520], ids=["short_loop", "deep_loop"])
+def test_wg_spec_64x64_grid_larger_than_resident(K):
     """64 x 64 tiles take up to four workgroups per CU in a WG_SPEC call; the
-    grid that runs holds one per CU.  Results as from a fused call."""
-    p = Problem(2, 1300, 1288, 136, "f16", 64, 64, seed=3)
+    grid that runs holds one per CU (the most that are resident, for either
+    K loop), so the consumers never wait for a producer that has no CU.
+    Results as from a fused call."""
+    from paper_2511_12500_amd import trace as T
+    p = Problem(2, 1300, 1288, K, "f16", 64, 64, seed=3)
     cus, limit = sym().symtile_device_info(0, 64, 64)
-    assert limit >= 4 * cus
+    assert limit == 4 * cus
     p.sentinel()
     p.run(0, FUSED)
     p.barrier()
     ref = u16(p.out.C_all()).copy()
     for copy_wgs in (1, limit // 4, limit - 1):
         p.sentinel()
-        p.run(0, WGSPEC, gemm_wgs=limit - copy_wgs, copy_wgs=copy_wgs)
+        tr = p.out.new_trace()
+        p.run(0, WGSPEC, gemm_wgs=limit - copy_wgs, copy_wgs=copy_wgs, trace=tr)
         p.barrier()
         assert np.array_equal(u16(p.out.C_all()), ref), copy_wgs
+        raw = tr.cpu().numpy().view(np.uint64)
+        assert int((raw[:, T.WHERE] & np.uint64(0xFFFF)).max()) < cus
     with pytest.raises(sym().SymtileError) as e:
         p.run(0, WGSPEC, gemm_wgs=limit, copy_wgs=1)
     assert e.value.name == "EUNSUPPORTED"
