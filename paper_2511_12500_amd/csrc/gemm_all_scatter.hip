@@ -200,6 +200,17 @@ __device__ __forceinline__ GasCall unpack(const GasParams& a) {
     return c;
 }
 
+// The call of a kernel that never runs with split-K (the host starts it with
+// split = 1), so that none of the split-K code is compiled into it.
+__device__ __forceinline__ GasCall unpack_unsplit(const GasParams& a) {
+    GasCall c = unpack(a);
+    c.split = 1;
+    c.sk_band = 0;
+    c.by_split = Div{1u << 31, 0};
+    c.units = c.num_tiles;
+    return c;
+}
+
 // Trace record of tile (tm, tn), or nullptr when tracing is off.
 __device__ __forceinline__ uint64_t* tile_trace(const GasCall& p, int tm, int tn) {
     return p.trace ? p.trace + ((size_t)tm * p.tiles_n + tn) * SYMTILE_TRACE_WORDS : nullptr;
@@ -1795,7 +1806,10 @@ template <int BM, int BN, bool BF16, int NW, int MF, bool SHORT>
 __global__ __launch_bounds__(64 * NW)
 __attribute__((amdgpu_waves_per_eu(NW / 4, NW / 4)))
 void gas_pc_kernel(const GasParams a) {
-    gas_body<BM, BN, BF16, NW, MF, false, false, SHORT, true>(unpack(a));
+    // (4-wave 256 x 256: without the split-K code the compiler drains every load
+    // at the head of the K loop, bf16 4096x4096x2048, w = 4: 107 -> 119 us)
+    constexpr bool V4 = BM == 256 && BN == 256 && NW == 4;
+    gas_body<BM, BN, BF16, NW, MF, false, false, SHORT, true>(V4 ? unpack(a) : unpack_unsplit(a));
 }
 
 // The 32-k ring for short K (see loop_cfg).
@@ -1803,7 +1817,7 @@ template <int BM, int BN, bool BF16, int NW>
 __global__ __launch_bounds__(64 * NW)
 __attribute__((amdgpu_waves_per_eu(NW / 4, NW / 4)))
 void gas_short_kernel(const GasParams a) {
-    gas_body<BM, BN, BF16, NW, 32, false, false, true, false>(unpack(a));
+    gas_body<BM, BN, BF16, NW, 32, false, false, true, false>(unpack_unsplit(a));
 }
 
 // Copy kernels of the bulk-synchronous and unfused producer-consumer

@@ -519,6 +519,25 @@ def test_four_and_eight_wave_kernels_agree_bitwise(case):
     assert np.array_equal(heaps[0], heaps[1])
 
 
+@pytest.mark.parametrize("variant", [WGSPEC, UNFUSED], ids=VNAMES.get)
+@pytest.mark.parametrize("K", [200, 4096])
+def test_four_wave_256_producers_match_fused_bitwise(variant, K):
+    """The 4-wave 256 x 256 loop as the producers of the producer-consumer
+    schedules, with one tile and with several per producer."""
+    p = Problem(4, 1000, 1032, K, "bf16", 256, 256, seed=15)
+    want = {1: oracle_block(p.A, p.shards[1], "bf16")}
+    p.sentinel()
+    p.run(1, FUSED)
+    p.barrier()
+    ref = u16(p.out.C_all()).copy()
+    for g, c in ((20, 4), (3, 2)):
+        p.sentinel()
+        p.run(1, variant, waves_per_wg=4, gemm_wgs=g, copy_wgs=c)
+        p.barrier()
+        check_gathered(p, want)
+        assert np.array_equal(u16(p.out.C_all()), ref)
+
+
 @pytest.mark.parametrize("split", [2, 3])
 def test_four_wave_256_split_k_matches_eight_waves_bitwise(split):
     """256 x 256 tiles with 4 waves stage 64 k at a time; K slices of an odd

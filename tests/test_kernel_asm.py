@@ -28,10 +28,13 @@ SRC = os.path.join(B.CSRC, "gemm_all_scatter.hip")
 pytestmark = pytest.mark.skipif(not (os.path.exists(HIPCC) or shutil.which("hipcc")),
                                 reason="hipcc not installed")
 
-# gas_kernel<256, 256, BF16, 4 waves, MF = 32, no copy wave, not the reduction kernel>
+# gas_kernel<256, 256, BF16, 4 waves, MF = 32, no copy wave, not the reduction kernel> and
+# gas_pc_kernel<256, 256, BF16, 4 waves, MF = 32, not for short K>
 KERNELS = {
     "bf16": "_ZN12_GLOBAL__N_110gas_kernelILi256ELi256ELb1ELi4ELi32ELb0ELb0EEEvNS_9GasParamsE",
     "f16": "_ZN12_GLOBAL__N_110gas_kernelILi256ELi256ELb0ELi4ELi32ELb0ELb0EEEvNS_9GasParamsE",
+    "pc_bf16": "_ZN12_GLOBAL__N_113gas_pc_kernelILi256ELi256ELb1ELi4ELi32ELb0EEEvNS_9GasParamsE",
+    "pc_f16": "_ZN12_GLOBAL__N_113gas_pc_kernelILi256ELi256ELb0ELi4ELi32ELb0EEEvNS_9GasParamsE",
 }
 
 
@@ -92,16 +95,16 @@ def accumulator_hazards(body, window=40):
     return bad
 
 
-@pytest.mark.parametrize("dtype", sorted(KERNELS))
-def test_no_accumulator_access_next_to_the_mfmas(asm, dtype):
-    body = function_body(asm, KERNELS[dtype])
+@pytest.mark.parametrize("kernel", sorted(KERNELS))
+def test_no_accumulator_access_next_to_the_mfmas(asm, kernel):
+    body = function_body(asm, KERNELS[kernel])
     assert sum(l.startswith("v_mfma") for l in body) >= 64
     assert accumulator_hazards(body) == []
 
 
-@pytest.mark.parametrize("dtype", sorted(KERNELS))
-def test_k_loop_has_no_spills_copies_or_drains(asm, dtype):
-    loop = instructions(k_loop(function_body(asm, KERNELS[dtype])))
+@pytest.mark.parametrize("kernel", sorted(KERNELS))
+def test_k_loop_has_no_spills_copies_or_drains(asm, kernel):
+    loop = instructions(k_loop(function_body(asm, KERNELS[kernel])))
     ops = [l.split()[0] for l in loop]
     assert sum(o.startswith("v_mfma") for o in ops) == 128        # two 64-k stages
     assert not [o for o in ops if o.startswith(("scratch_", "v_accvgpr", "v_readlane",
@@ -110,6 +113,19 @@ def test_k_loop_has_no_spills_copies_or_drains(asm, dtype):
     assert not [w for w in waits if re.search(r"vmcnt\(0\)", w)]
     # every staging register goes to LDS only after its own load: exact waits
     assert any(re.search(r"vmcnt\((1[0-9]|[1-9])\)", w) for w in waits)
+
+
+def test_kernels_for_unsplit_calls_hold_no_split_k_code(asm):
+    """The producer-consumer kernels and the ones for short K never run with
+    split-K; its counters' resets (atomic exchanges) show whether its code was
+    compiled in.  The 4-wave 256 x 256 kernels keep it (their K loop is
+    checked above)."""
+    names = [m.group(1) for m in (re.match(r"(_ZN\S*gas_(?:pc|short)_kernel\S*):", l) for l in asm)
+             if m and not re.search("ILi256ELi256ELb[01]ELi4E", m.group(1))]
+    assert len(names) == 18
+    for name in names:
+        body = function_body(asm, name)
+        assert not [l for l in body if l.startswith(("global_atomic_swap", "scratch_"))], name
 
 
 # ---------------------------------------------------------------- two grids side by side
