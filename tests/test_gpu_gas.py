@@ -1009,6 +1009,9 @@ def test_wg_spec_64x64_grid_larger_than_resident(K):
     (3, 520, 264, 2048, 128, 128, 7, 1),    # one consumer, few slots each
     (8, 520, 264, 40, 128, 128, 4, 9),      # more consumers than producers
     (8, 600, 264, 8, 64, 64, 60, 40),       # one tile per producer
+    (8, 200, 264, 264, 64, 64, 20, 20),     # as many consumers as tiles: whole workgroups
+    (5, 300, 264, 200, 128, 128, 4, 9),     # ... for 128x128 tiles
+    (4, 300, 264, 200, 128, 128, 4, 8),     # one tile more than consumers: single waves
     (7, 700, 264, 264, 256, 128, 2, 200),   # more consumers than tiles
     (8, 700, 520, 520, 256, 256, 3, 2),
 ], ids=lambda c: "w%d_m%d_n%d_k%d_t%dx%d_g%d_c%d" % c)
