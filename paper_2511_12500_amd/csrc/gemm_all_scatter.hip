@@ -1987,10 +1987,16 @@ symtile_status coresident_limit(const Variant* v, int device, int* cus, int* lim
 // workgroups and 729 with 248 + 8, against 230 for the fused call).  So each
 // takes the share of the slots that its workgroups are of the grid, the
 // consumers at least one.
-// Tiles before the last.  The consumers take what they can move during one
-// tile's K loop, at 50 GB/s per workgroup and 4.5 TFLOP/s per producer (what
-// both reach on the large shapes), and at least one slot; the producers
-// store the rest, which would only queue up behind the consumers.
+// Tiles before the last.  A producer's tile takes its K loop (4.5 TFLOP/s), its
+// own and `mid` other slots' stores, some 4 us until its first loads are there
+// and its stores are acknowledged, and 1.5 us more for the second pass of
+// stores where mid > 0; the consumers put the other slots of `producers` tiles
+// meanwhile (50 GB/s per workgroup on both sides, what they reach on the large
+// shapes).  The `mid` that makes the longer of the two shortest, the consumers
+// at least one slot.  With short K loops the two latencies decide (w = 8,
+// K = 512, us a call with mid 0 .. 6: 4096x2048 in 64x64 tiles, 128 + 128
+// workgroups 85 100 114 120 121 124 126; the same in 256x128 tiles, 224 + 32
+// workgroups 50 50 48 48 47 46 44).
 void share_slots(GasCall& p, int bm, int bn, int g, int c) {
     const int others = p.world - 1;
     p.direct_last = p.direct_mid = 0;
@@ -1998,9 +2004,16 @@ void share_slots(GasCall& p, int bm, int bn, int g, int c) {
     const int producers = std::min(g, p.num_tiles);
     const int last = (int)(others * (double)c / (producers + c) + 0.5);
     p.direct_last = others - std::min(std::max(last, 1), others);
-    const double loop_s = 2.0 * bm * bn * (double)p.K / 4.5e12;
-    const double slots = c * 50e9 * loop_s / ((double)producers * bm * bn * 2);
-    p.direct_mid = others - (int)std::min(std::max(slots, 1.0), (double)others);
+    const double loop_s = 2.0 * bm * bn * (double)p.K / 4.5e12, slot_s = 2.0 * bm * bn / 50e9;
+    double best = 0;
+    for (int mid = 0; mid < others; ++mid) {
+        const double produce = loop_s + 4e-6 + (mid > 0 ? 1.5e-6 : 0) + (1 + mid) * slot_s;
+        const double s = std::max(produce, (others - mid) * slot_s * producers / c);
+        if (mid == 0 || s < best) {
+            best = s;
+            p.direct_mid = mid;
+        }
+    }
 }
 
 // The divisors of a call, once everything else is set.

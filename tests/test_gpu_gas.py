@@ -1014,6 +1014,8 @@ def test_wg_spec_64x64_grid_larger_than_resident(K):
     (4, 300, 264, 200, 128, 128, 4, 8),     # one tile more than consumers: single waves
     (7, 700, 264, 264, 256, 128, 2, 200),   # more consumers than tiles
     (8, 700, 520, 520, 256, 256, 3, 2),
+    (8, 600, 520, 256, 64, 64, 30, 4),      # short K: the producers store some slots of every tile
+    (8, 600, 520, 520, 64, 64, 12, 12),     # ... none but of their last
 ], ids=lambda c: "w%d_m%d_n%d_k%d_t%dx%d_g%d_c%d" % c)
 def test_slots_shared_by_producers_and_consumers(case, variant):
     """Whatever share of the slots the producers store themselves, every slot
