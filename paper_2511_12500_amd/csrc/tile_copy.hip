@@ -309,7 +309,7 @@ static symtile_status tile_copy_launch(symtile_heap* h, size_t src_off, size_t d
     p.row_chunks = (int)((size_t)cols * esize / 16);
     p.ld_bytes = (int)ld_bytes;
     p.tile_r = tile_r;
-    p.tile_chunks = (int)((size_t)tile_c * esize / 16);
+    p.tile_chunks = (int)((size_t)std::min(tile_c, cols) * esize / 16);
     p.tiles_c = tiles_c;
     p.ntiles = (int)ntiles;
     const size_t nitems = ntiles * (only_rank >= 0 ? 1 : (size_t)h->world);

@@ -546,8 +546,8 @@ def test_litmus_rejects_bad_arguments():
     (4, 300, 1160, 64, 64, "bf16"), (2, 130, 2040, 64, 24, "f16"), (8, 33, 260, 32, 4, "f32"),
     (3, 64, 8, 64, 8, "bf16"), (1, 70, 1000, 7, 40, "f32"), (2, 20, 16384, 16, 16384, "f32"),
     (2, 9, 12304, 8, 4104, "bf16"), (8, 520, 2048, 128, 128, "f32"),
-    # tiles that leave waves of a workgroup without a chunk
-    (2, 200, 24, 8, 8, "bf16"), (4, 100, 48, 15, 24, "bf16"),
+    # tiles that leave waves of a workgroup without a chunk, tiles wider than the matrix
+    (2, 200, 24, 8, 8, "bf16"), (4, 100, 48, 15, 24, "bf16"), (2, 64, 64, 64, 1 << 28, "f32"),
 ], ids=lambda c: "w%d_%dx%d_t%dx%d_%s" % c)
 def test_heap_tile_copy_automatic_runs(case, mode):
     """The library's own split of the tile rows into runs, and the caller's (one,
