@@ -235,8 +235,22 @@ constexpr size_t kStreamBytes = size_t(256) << 20;
 // wide.  Runs need not be equal (19 tiles a row used to mean one tile per
 // workgroup: bf16 1500x1160, 4 ranks, 64x64 tiles 23.4 -> 6.5 us a call;
 // fp32 1442x684, 8 ranks, 128x128 tiles 14.9 -> 12.0).
-int choose_segs(size_t bands, int tiles_c, size_t tile_bytes, int tile_chunks, size_t cus) {
+//
+// From kHugeBytes read and written on, memory alone sets the time, and runs of 1
+// KiB a row are best: the workgroups that are active together then cover whole
+// rows of a few tile rows (us with the rule above -> so: fp32 8192x8192, 8 ranks,
+// 128x128 tiles 715 -> 677, 64x64 767 -> 687; 16384x8192, 2 ranks, 256x256 389 ->
+// 346; bf16 8192x8192, 8 ranks, 128x128 429 -> 393; at half of it some calls lose:
+// fp32 8192x8192, 2 ranks, 128x128 170 -> 184).
+constexpr size_t kHugeBytes = size_t(2) << 30;
+constexpr int kHugeWidth = 1024 / 16;      // chunks
+int choose_segs(size_t bands, int tiles_c, size_t tile_bytes, int tile_chunks, size_t cus,
+                size_t call_bytes) {
     constexpr size_t kRunBytes = 32 << 10;
+    if (call_bytes >= kHugeBytes) {
+        const int per = std::max(1, kHugeWidth / tile_chunks);
+        return (tiles_c + per - 1) / per;
+    }
     const size_t widest = std::max<size_t>(1, (size_t)kThreads / tile_chunks);
     size_t best = 0, best_cost = SIZE_MAX;
     for (size_t r = 1; r <= 2; ++r) {      // runs per CU (where the tile rows are fewer)
@@ -351,8 +365,10 @@ static symtile_status tile_copy_launch(symtile_heap* h, size_t src_off, size_t d
     }
     p.tiles_r = tiles_r;
     const size_t bands = (size_t)tiles_r * (only_rank >= 0 ? 1 : (size_t)h->world);
+    const size_t call_bytes = 2 * (size_t)rows * cols * esize * (bands / tiles_r);
     p.segs = automatic ? choose_segs(bands, tiles_c, (size_t)tile_r * tile_c * esize, p.tile_chunks,
-                                     (size_t)std::max(1, symtile_host::cu_count(h->device)))
+                                     (size_t)std::max(1, symtile_host::cu_count(h->device)),
+                                     call_bytes)
              : band_lg_w >= 0 ? tiles_c / tiles_per_wg
                               : 0;
     const int run_tiles = p.segs ? (tiles_c + p.segs - 1) / p.segs : 1;
@@ -377,7 +393,7 @@ static symtile_status tile_copy_launch(symtile_heap* h, size_t src_off, size_t d
     if (symtile_status st = symtile_host::set_device(h, &prev)) return st;
     const dim3 grid((unsigned)(p.segs ? bands * p.segs : (nitems + p.per_wg - 1) / p.per_wg));
     hipStream_t stream = static_cast<hipStream_t>(s);
-    const bool stream_loads = 2 * (size_t)rows * cols * esize * (bands / tiles_r) >= kStreamBytes;
+    const bool stream_loads = call_bytes >= kStreamBytes;
     const bool small = (size_t)tile_r * p.width <= kThreads - 64;
     const void* kernel =
         !p.segs        ? p.lg_w >= 0 ? reinterpret_cast<const void*>(&tile_list_copy_kernel<true>)

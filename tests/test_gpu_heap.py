@@ -577,3 +577,24 @@ def test_heap_tile_copy_automatic_runs(case, mode):
                                     only_rank=only, get=bool(mode))
         assert np.array_equal(recv, want), (only, shift, per)
         assert np.array_equal(fl, wf.astype(np.int32)), (only, shift, per)
+
+
+def test_heap_tile_copy_two_gib_call():
+    """From 2 GiB read and written on the tile rows are cut into narrow runs: every
+    block and counter as for smaller calls (rows and columns end inside a tile)."""
+    pkg = sym()
+    world, rows, cols, t = 8, 4100, 8200, 128
+    heap, src, dst, flags = _copy_heap(pkg, world, rows, cols, torch.float32)
+    send = heap.slots_view(src, (rows, cols), torch.int32)
+    for r in range(world):
+        send[r].random_(-2 ** 31, 2 ** 31)
+    tiles = (-(-rows // t), -(-cols // t))
+    heap.slots_view(dst, (rows, cols), torch.int32).zero_()
+    heap.slots_view(flags, tiles, torch.int32).zero_()
+    pkg.symtile_tile_copy(heap.handle, src, dst, rows, cols, cols, pkg.F32, t, t, 3, -1, flags,
+                          stream=pkg.current_stream())
+    heap.barrier()
+    recv = heap.slots_view(dst, (rows, cols), torch.int32)
+    for r in range(world):
+        assert torch.equal(recv[(r + 3) % world], send[r]), r
+    assert bool((heap.slots_view(flags, tiles, torch.int32) == 1).all())
