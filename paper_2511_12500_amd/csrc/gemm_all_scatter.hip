@@ -1922,15 +1922,18 @@ Variant make_short_variant() {
 
 constexpr int kShortK = 256;
 
-// Tiles per rank up to which the library's choice of store policy (0) writes
-// back.  A write-through store is acknowledged by memory, later than by the
-// L2, and the more slots a tile is stored to, the longer that takes, once per
-// call; the release of write-back stores walks the L2 once per tile, and an
-// XCD's tiles (one in eight) pay one after another.  K = 256, 64x64 tiles,
-// write-back / written through, us: w = 2, 16 tiles 5.95 / 5.96, 64 tiles 6.33
-// / 6.03; w = 8, 4 tiles 7.27 / 8.25, 64 tiles 8.11 / 8.53.  With many tiles
-// (fp16 8192x512x1024, w = 8): fused 121 / 69, bulk-synchronous 157 / 74,
-// WG_SPEC 268 / 99.
+// Unsplit fused calls of up to kWriteBackTiles tiles for each rank of the world
+// write back, unless the caller asks for write-through.  A write-through store
+// (streaming or not) is acknowledged by memory, later than by the L2, and the
+// more slots a tile is stored to, the longer that takes, once per call; the
+// release of write-back stores walks the L2 once per tile, and an XCD's tiles
+// (one in eight) pay one after another.  Us, write-back / written through:
+// 64x64 tiles, K = 256: w = 2, 16 tiles 5.95 / 5.96, 64 tiles 6.33 / 6.03; w =
+// 8, 4 tiles 7.27 / 8.25, 64 tiles 8.11 / 8.53; K = 1024, w = 8: 8 tiles 8.6 /
+// 9.8.  K = 1024, w = 8, 64 tiles of 256x256 42.5 / 45.9 (streaming 46.2), 32 of
+// 256x128 21.9 / 23.4, 32 of 128x128 15.1 / 15.4; w = 2, 64 of 256x256 31.0 /
+// 30.3.  With many tiles (fp16 8192x512x1024, w = 8): fused 121 / 69,
+// bulk-synchronous 157 / 74, WG_SPEC 268 / 99.
 constexpr size_t kWriteBackTiles = 8;
 
 // waves == 0 picks the first entry of the shape (the default wave count);
@@ -2228,9 +2231,11 @@ extern "C" symtile_status symtile_gemm_all_scatter(
     if (cfg.nontemporal < 0 || cfg.nontemporal > 2)
         return fail(SYMTILE_EINVAL, "nontemporal must be 0, 1 or 2");
     p.nontemporal = cfg.nontemporal;
-    if (cfg.nontemporal == 0 && (cfg.variant != SYMTILE_FUSED_SEQ || split > 1 ||
-                                 num_tiles > kWriteBackTiles * world_size))
-        p.nontemporal = 2;
+    if (cfg.nontemporal != 2)
+        p.nontemporal = cfg.variant == SYMTILE_FUSED_SEQ && split == 1 &&
+                                num_tiles <= kWriteBackTiles * world_size
+                            ? 0
+                            : cfg.nontemporal == 1 ? 1 : 2;
     p.trace = cfg.trace;
     p.copy_wgs = 0;
     p.split = split;

@@ -240,7 +240,7 @@ constexpr size_t kStreamBytes = size_t(256) << 20;
 // KiB a row are best: the workgroups that are active together then cover whole
 // rows of a few tile rows (us with the rule above -> so: fp32 8192x8192, 8 ranks,
 // 128x128 tiles 715 -> 677, 64x64 767 -> 687; 16384x8192, 2 ranks, 256x256 389 ->
-// 346; bf16 8192x8192, 8 ranks, 128x128 429 -> 393; at half of it some calls lose:
+// 346; bf16 8192x8192, 8 ranks, 128x128 429 -> 347; at half of it some calls lose:
 // fp32 8192x8192, 2 ranks, 128x128 170 -> 184).
 constexpr size_t kHugeBytes = size_t(2) << 30;
 constexpr int kHugeWidth = 1024 / 16;      // chunks
