@@ -1471,35 +1471,46 @@ __device__ __forceinline__ void gas_body(const GasCall& p) {
                         }
                 }
             };
-            // dst = partial q (first) or dst + partial q, in batches of 8
-            // loads (32 registers): scheduling fences keep the compiler from
-            // hoisting every load at once, which would need 4 registers per
-            // accumulator register.  Blocks outside the covered set are not
-            // touched.
-            auto add_partial = [&](acc_t (&dst)[MI][NI], int q, bool first) {
-                const symtile::rsrc_t rs = slot(q);
-                constexpr int GPA = ACC_N / 4;                 // 4-value groups per accumulator
-                constexpr int NG = MI * NI * GPA;
-                constexpr int BATCH = NG % 8 == 0 ? 8 : NG % 4 == 0 ? 4 : 1;
-                static_assert(NG % BATCH == 0, "batch split");
+            // dst = partial q (first) or dst + partial q, then + partials q + 1 ..
+            // q + count - 1 (count <= QB), in batches of 8 loads (32 registers):
+            // scheduling fences keep the compiler from hoisting every load at
+            // once, which would need 4 registers per accumulator register.  A
+            // wave of the 64 x 64 tile has two loads per slice, so four slices
+            // make a batch (64x8192x1024, w = 4, 64 slices, last arriver:
+            // LASTA -> LASTB us).  Blocks outside the covered set are not touched.
+            constexpr int GPA = ACC_N / 4;                     // 4-value groups per accumulator
+            constexpr int NG = MI * NI * GPA;
+            constexpr int BATCH = NG % 8 == 0 ? 8 : NG % 4 == 0 ? 4 : NG;
+            constexpr int QB = kBig ? 1 : 8 / BATCH;
+            static_assert(NG % BATCH == 0 && BATCH <= 8, "batch split");
+            auto add_partial = [&](acc_t (&dst)[MI][NI], int q, int count, bool first) {
 #pragma unroll
                 for (int b = 0; b < NG; b += BATCH) {
-                    symtile::u32x4 v[BATCH];
+                    symtile::u32x4 v[QB][BATCH];
 #pragma unroll
-                    for (int x = 0; x < BATCH; ++x) {
-                        const int i = (b + x) / (NI * GPA);
-                        v[x] = symtile::buf_ld16p<symtile::kLoadCoherent>(
-                            rs, covered(i, true) ? part_lane : symtile::kOOB,
-                            (uint32_t)((b + x) * 1024));
+                    for (int s = 0; s < QB; ++s) {
+                        const symtile::rsrc_t rs = slot(q + min(s, count - 1));
+#pragma unroll
+                        for (int x = 0; x < BATCH; ++x) {
+                            const int i = (b + x) / (NI * GPA);
+                            v[s][x] = symtile::buf_ld16p<symtile::kLoadCoherent>(
+                                rs, s < count && covered(i, true) ? part_lane : symtile::kOOB,
+                                (uint32_t)((b + x) * 1024));
+                        }
                     }
 #pragma unroll
-                    for (int x = 0; x < BATCH; ++x) {
-                        const int n = b + x, i = n / (NI * GPA), j = (n / GPA) % NI, g = n % GPA;
-                        if (!covered(i, true)) continue;
-                        const f32x4_t y = __builtin_bit_cast(f32x4_t, v[x]);   // whole vector
+                    for (int s = 0; s < QB; ++s) {
+                        if (s >= count) continue;              // uniform
 #pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            dst[i][j][4 * g + e] = first ? y[e] : dst[i][j][4 * g + e] + y[e];
+                        for (int x = 0; x < BATCH; ++x) {
+                            const int n = b + x, i = n / (NI * GPA), j = (n / GPA) % NI, g = n % GPA;
+                            if (!covered(i, true)) continue;
+                            const f32x4_t y = __builtin_bit_cast(f32x4_t, v[s][x]);   // whole vector
+#pragma unroll
+                            for (int e = 0; e < 4; ++e)
+                                dst[i][j][4 * g + e] =
+                                    first && s == 0 ? y[e] : dst[i][j][4 * g + e] + y[e];
+                        }
                     }
                     __builtin_amdgcn_sched_barrier(0);
                 }
@@ -1512,7 +1523,6 @@ __device__ __forceinline__ void gas_body(const GasCall& p) {
                 // of a partial (4 consecutive columns of one row), taken so that
                 // a wave reads 1 KiB runs; CH chunks of QB
                 // slices are in flight per thread at once.
-                constexpr int GPA = ACC_N / 4;
                 constexpr int PER_BR = NI * GPA * WGN * 64;    // chunks per block row
                 constexpr int CH = 4, QB = 4;
                 const int total = band_rows / MF * PER_BR;
@@ -1622,7 +1632,8 @@ __device__ __forceinline__ void gas_body(const GasCall& p) {
                     // (p0 + ... + p(ks-1)) + p(ks) since addition commutes, then
                     // acc += p(ks+1), ... in slice order.
                     acc_t tmp[MI][NI];
-                    for (int q = 0; q < ks; ++q) add_partial(tmp, q, q == 0);
+                    for (int q = 0; q < ks; q += QB)
+                        add_partial(tmp, q, min(QB, ks - q), q == 0);
                     if (ks > 0) {
     #pragma unroll
                         for (int i = 0; i < MI; ++i)
@@ -1632,7 +1643,8 @@ __device__ __forceinline__ void gas_body(const GasCall& p) {
                                 for (int e = 0; e < ACC_N; ++e)
                                     if (covered(i, true)) acc[i][j][e] = tmp[i][j][e] + acc[i][j][e];
                     }
-                    for (int q = ks + 1; q < p.split; ++q) add_partial(acc, q, false);
+                    for (int q = ks + 1; q < p.split; q += QB)
+                        add_partial(acc, q, min(QB, p.split - q), false);
                 } else {
                     // Two slices: acc + the other partial, which is p0 + p1 either
                     // way (fp32 addition commutes).  More: this slice's partial
@@ -1642,7 +1654,7 @@ __device__ __forceinline__ void gas_body(const GasCall& p) {
                     // loop.)
                     const int nq = p.split == 2 ? 1 : p.split;
                     for (int n = 0; n < nq; ++n)
-                        add_partial(acc, p.split == 2 ? 1 - ks : n, p.split != 2 && n == 0);
+                        add_partial(acc, p.split == 2 ? 1 - ks : n, 1, p.split != 2 && n == 0);
                 }
             }
         }
