@@ -83,8 +83,8 @@ typedef struct {
                              write-back for FUSED_SEQ calls without split-K of up
                              to 8 * world_size tiles, else write-through (leaves
                              no dirty L2 line for the release to write back); 1
-                             streaming: the same with the non-temporal hint on
-                             write-through stores; 2 write-through */
+                             streaming: the library's choice too (the hint is
+                             never faster on these stores); 2 write-through */
     int group_m;          /* tile rows per L2 swizzle group; 0 = 4 */
     int waves_per_wg;     /* 4 or 8 picks the build of a 256x256 tile with that many
                              wavefronts per workgroup (4 stages 64 k at a time

@@ -107,10 +107,8 @@ __device__ __forceinline__ u32x4 buf_ld16(rsrc_t r, uint32_t voff, uint32_t soff
 //   kStoreNonTemporal  nt: streaming hint, the line is a preferred victim;
 //   kStoreWriteThrough sc0 sc1: system-scope coherence, written through the
 //                      L2 to memory (measured best for the cold heap copy,
-//                      where the destination is not read again soon);
-//   kStoreStreamThrough sc0 sc1 nt: written through, with the streaming hint.
-enum : int { kStoreDefault = 0, kStoreNonTemporal = 2, kStoreWriteThrough = 17,
-             kStoreStreamThrough = 19 };
+//                      where the destination is not read again soon).
+enum : int { kStoreDefault = 0, kStoreNonTemporal = 2, kStoreWriteThrough = 17 };
 
 // Load cache policies: kLoadDefault may hit a line this XCD's L2 holds from
 // before; kLoadCoherent (sc0 sc1, the encoding the memory model gives a

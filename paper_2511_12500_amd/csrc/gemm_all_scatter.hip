@@ -394,27 +394,25 @@ __device__ __forceinline__ uint32_t tile_span(int rows_valid, int cols_valid, in
     return (uint32_t)(((size_t)(rows_valid - 1) * ldc + cols_valid) * 2);
 }
 
-// Store policy of the output (GasCall::nontemporal): 1 written through to
-// memory with the streaming hint, 2 written through, 0 write-back, which the
-// host picks for small unsplit fused calls only (kWriteBackTiles).  Written
-// through, the L2 keeps no dirty line of the output and the stores'
-// acknowledgement is the release; written back, each tile's release is a
-// write-back of the XCD's L2.  Calls f with the cache-policy bits as a
-// compile-time constant.
-template <typename F>
-__device__ __forceinline__ void with_through_policy(int mode, F&& f) {
-    if (mode == 1)
-        f(std::integral_constant<int, symtile::kStoreStreamThrough>{});
-    else
-        f(std::integral_constant<int, symtile::kStoreWriteThrough>{});
-}
-
+// Store policy of the output (GasCall::nontemporal): 2 written through to
+// memory, 0 write-back, which the host picks for small unsplit fused calls
+// only (kWriteBackTiles).  Written through, the L2 keeps no dirty line of the
+// output and the stores' acknowledgement is the release; written back, each
+// tile's release is a write-back of the XCD's L2.  Calls f with the
+// cache-policy bits as a compile-time constant.
+//
+// The caller's streaming policy (1) is the library's choice too.  The
+// non-temporal hint on written-through stores was never faster and costs where
+// the tile is read back (us with / without it; bf16, w = 8 unless given: fused
+// 4096x136x4096, w = 2, 256x256 tiles 26.2 / 23.7; WG_SPEC 2048x128x1024,
+// 256x256 tiles, 192 + 64 workgroups 30.1 / 22.4; WAVE_SPEC 8192x136x2048 106 /
+// 63; bulk 2048x128x1024, 256x256 tiles 39.7 / 34.9).
 template <typename F>
 __device__ __forceinline__ void with_store_policy(int mode, F&& f) {
     if (mode == 0)
         f(std::integral_constant<int, symtile::kStoreDefault>{});
     else
-        with_through_policy(mode, f);
+        f(std::integral_constant<int, symtile::kStoreWriteThrough>{});
 }
 
 // Release of this workgroup's output stores before their counters move
@@ -448,12 +446,12 @@ __device__ __forceinline__ uint16_t* out_tile_ptr(const GasCall& p, int BM, int 
 // d in [d0, world) (the put of Sections 4.1.1 and 4.2.2), and release its
 // counters there, by THREADS threads (a workgroup or one wave).  LOAD is the
 // policy of the tile's loads (coherent after a flag_wait_coherent).
-template <int BM, int BN, int THREADS, int POLICY, int LOAD = symtile::kLoadDefault>
+template <int BM, int BN, int THREADS, int LOAD = symtile::kLoadDefault>
 __device__ void put_tile_to_peers(const GasCall& p, int tm, int tn, int tid, int d0) {
     using IO = TileIO<BM, BN, THREADS>;
-    symtile::put_ranks<POLICY, IO::U, LOAD>(out_tile_ptr(p, BM, BN, tm, tn),
-                                            out_tile<BM, BN, THREADS>(p, tm, tn), p.rank, d0,
-                                            p.world, p.world, p.bases, tid, THREADS);
+    symtile::put_ranks<symtile::kStoreWriteThrough, IO::U, LOAD>(
+        out_tile_ptr(p, BM, BN, tm, tn), out_tile<BM, BN, THREADS>(p, tm, tn), p.rank, d0, p.world,
+        p.world, p.bases, tid, THREADS);
     if constexpr (THREADS > 64)
         symtile::wg_stores_done();
     else
@@ -515,12 +513,8 @@ __device__ __forceinline__ void consume_tiles_by(const GasCall& p, int cid, int 
             ok = s_ok;
         }
         if (!ok) return;
-        with_through_policy(p.nontemporal, [&](auto pol) {
-            constexpr int P = decltype(pol)::value;
-            put_tile_to_peers<BM, BN, MOVERS, P, symtile::kLoadCoherent>(
-                p, tm, tn, tid,
-                1 + (t + p.gemm_wgs >= p.num_tiles ? p.direct_last : p.direct_mid));
-        });
+        put_tile_to_peers<BM, BN, MOVERS, symtile::kLoadCoherent>(
+            p, tm, tn, tid, 1 + (t + p.gemm_wgs >= p.num_tiles ? p.direct_last : p.direct_mid));
         if (tr && tid == 0) tr[SYMTILE_TRACE_COPY_DONE] = symtile::clock_now();
     }
 }
@@ -548,7 +542,7 @@ __device__ void consume_tiles(const GasCall& p, int cid, int ncons) {
 // counter, so each interval issues its load before its stores.  With fewer
 // barriers than that needs (small K) the wave stores each group as soon as
 // it is loaded.
-template <int BM, int BN, int POLICY>
+template <int BM, int BN>
 __device__ void copy_wave_tiles(const GasCall& p, int stages) {
     constexpr int CPR = staged_width(BN) / 8;   // 16-byte chunks per tile row
     constexpr int RPI = 64 / CPR;               // tile rows per wave-wide access
@@ -588,7 +582,8 @@ __device__ void copy_wave_tiles(const GasCall& p, int stages) {
         auto store_group = [&](const symtile::u32x4& v, int g) {
 #pragma unroll
             for (int d = 0; d < MAXW - 1; ++d)       // dropped past the world (empty resource)
-                symtile::buf_st16p<POLICY>(v, rd[d], voff, (uint32_t)g * group_bytes);
+                symtile::buf_st16p<symtile::kStoreWriteThrough>(v, rd[d], voff,
+                                                                (uint32_t)g * group_bytes);
         };
         auto publish = [&]() {
             __builtin_amdgcn_s_waitcnt(vm_wait(0));
@@ -765,9 +760,7 @@ __device__ __forceinline__ void gas_body(const GasCall& p) {
         // that the compiler keeps the copy wave's addressing scalar
         if (__builtin_amdgcn_readfirstlane(wave) == NW) {
             const int stages = DEEP ? (KT_all * BK + DBK - 1) / DBK : KT_all;
-            with_through_policy(p.nontemporal, [&](auto pol) {
-                copy_wave_tiles<BM, BN, decltype(pol)::value>(p, stages);
-            });
+            copy_wave_tiles<BM, BN>(p, stages);
             return;
         }
     }
@@ -1477,7 +1470,7 @@ __device__ __forceinline__ void gas_body(const GasCall& p) {
             // once, which would need 4 registers per accumulator register.  A
             // wave of the 64 x 64 tile has two loads per slice, so four slices
             // make a batch (64x8192x1024, w = 4, 64 slices, last arriver:
-            // LASTA -> LASTB us).  Blocks outside the covered set are not touched.
+            // 201 -> 88 us).  Blocks outside the covered set are not touched.
             constexpr int GPA = ACC_N / 4;                     // 4-value groups per accumulator
             constexpr int NG = MI * NI * GPA;
             constexpr int BATCH = NG % 8 == 0 ? 8 : NG % 4 == 0 ? 4 : NG;
@@ -1855,10 +1848,7 @@ __global__ __launch_bounds__(copy_threads<BM>()) void scatter_kernel(const GasPa
         uint64_t* tr = tile_trace(p, tm, tn);
         if (tr && threadIdx.x == 0)
             tr[SYMTILE_TRACE_COPY_WAIT] = tr[SYMTILE_TRACE_COPY_GO] = symtile::clock_now();
-        with_through_policy(p.nontemporal, [&](auto pol) {
-            put_tile_to_peers<BM, BN, copy_threads<BM>(), decltype(pol)::value>(p, tm, tn,
-                                                                                threadIdx.x, 1);
-        });
+        put_tile_to_peers<BM, BN, copy_threads<BM>()>(p, tm, tn, threadIdx.x, 1);
         if (tr && threadIdx.x == 0) tr[SYMTILE_TRACE_COPY_DONE] = symtile::clock_now();
     }
 }
@@ -1936,13 +1926,12 @@ constexpr int kShortK = 256;
 
 // Unsplit fused calls of up to kWriteBackTiles tiles for each rank of the world
 // write back, unless the caller asks for write-through.  A write-through store
-// (streaming or not) is acknowledged by memory, later than by the L2, and the
-// more slots a tile is stored to, the longer that takes, once per call; the
+// is acknowledged by memory, later than by the L2, and the more slots a tile is stored to, the longer that takes, once per call; the
 // release of write-back stores walks the L2 once per tile, and an XCD's tiles
 // (one in eight) pay one after another.  Us, write-back / written through:
 // 64x64 tiles, K = 256: w = 2, 16 tiles 5.95 / 5.96, 64 tiles 6.33 / 6.03; w =
 // 8, 4 tiles 7.27 / 8.25, 64 tiles 8.11 / 8.53; K = 1024, w = 8: 8 tiles 8.6 /
-// 9.8.  K = 1024, w = 8, 64 tiles of 256x256 42.5 / 45.9 (streaming 46.2), 32 of
+// 9.8.  K = 1024, w = 8, 64 tiles of 256x256 42.5 / 45.9, 32 of
 // 256x128 21.9 / 23.4, 32 of 128x128 15.1 / 15.4; w = 2, 64 of 256x256 31.0 /
 // 30.3.  With many tiles (fp16 8192x512x1024, w = 8): fused 121 / 69,
 // bulk-synchronous 157 / 74, WG_SPEC 268 / 99.
@@ -2242,12 +2231,10 @@ extern "C" symtile_status symtile_gemm_all_scatter(
     p.spin_limit = cfg.spin_limit;
     if (cfg.nontemporal < 0 || cfg.nontemporal > 2)
         return fail(SYMTILE_EINVAL, "nontemporal must be 0, 1 or 2");
-    p.nontemporal = cfg.nontemporal;
-    if (cfg.nontemporal != 2)
-        p.nontemporal = cfg.variant == SYMTILE_FUSED_SEQ && split == 1 &&
-                                num_tiles <= kWriteBackTiles * world_size
-                            ? 0
-                            : cfg.nontemporal == 1 ? 1 : 2;
+    p.nontemporal = cfg.nontemporal != 2 && cfg.variant == SYMTILE_FUSED_SEQ && split == 1 &&
+                            num_tiles <= kWriteBackTiles * world_size
+                        ? 0
+                        : 2;
     p.trace = cfg.trace;
     p.copy_wgs = 0;
     p.split = split;

@@ -162,3 +162,11 @@ def test_copy_kernel_shares_no_cu_with_a_producer(asm, tile):
     assert c <= 512 < 2 * c
     for name, r in prod.items():
         assert per_simd(*r) <= 512 < per_simd(*r) + c, name
+
+
+def test_output_stores_carry_no_streaming_hint(asm):
+    """A tile read back by its schedule's copy side (and, written through, any
+    tile) is stored without the non-temporal hint, whatever policy is asked for."""
+    stores = [l.strip() for l in asm if l.strip().startswith(("buffer_store", "global_store"))]
+    assert len(stores) > 1000
+    assert not [l for l in stores if re.search(r"\bnt\b", l)]
