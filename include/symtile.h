@@ -80,11 +80,12 @@ typedef struct {
     uint32_t spin_limit;  /* polls of one consumer wait before it gives up and
                              raises SYMTILE_ETIMEOUT; 0 = 1<<22 */
     int nontemporal;      /* store policy of the output: 0 the library's choice:
-                             write-back for FUSED_SEQ calls without split-K of up
-                             to 8 * world_size tiles, else write-through (leaves
-                             no dirty L2 line for the release to write back); 1
-                             streaming: the library's choice too (the hint is
-                             never faster on these stores); 2 write-through */
+                             write-back for small FUSED_SEQ and BULK_SYNC calls
+                             without split-K (a few tiles per rank), else
+                             write-through (leaves no dirty L2 line for the
+                             release to write back); 1 streaming: the library's
+                             choice too (the hint is never faster on these
+                             stores); 2 write-through */
     int group_m;          /* tile rows per L2 swizzle group; 0 = 4 */
     int waves_per_wg;     /* 4 or 8 picks the build of a 256x256 tile with that many
                              wavefronts per workgroup (4 stages 64 k at a time

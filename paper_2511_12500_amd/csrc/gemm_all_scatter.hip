@@ -395,11 +395,11 @@ __device__ __forceinline__ uint32_t tile_span(int rows_valid, int cols_valid, in
 }
 
 // Store policy of the output (GasCall::nontemporal): 2 written through to
-// memory, 0 write-back, which the host picks for small unsplit fused calls
-// only (kWriteBackTiles).  Written through, the L2 keeps no dirty line of the
-// output and the stores' acknowledgement is the release; written back, each
-// tile's release is a write-back of the XCD's L2.  Calls f with the
-// cache-policy bits as a compile-time constant.
+// memory, 0 write-back, which the host picks for small unsplit fused and
+// bulk-synchronous calls only (kWriteBackTiles).  Written through, the L2
+// keeps no dirty line of the output and the stores' acknowledgement is the
+// release; written back, each tile's release is a write-back of the XCD's L2.
+// Calls f with the cache-policy bits as a compile-time constant.
 //
 // The caller's streaming policy (1) is the library's choice too.  The
 // non-temporal hint on written-through stores was never faster and costs where
@@ -446,18 +446,21 @@ __device__ __forceinline__ uint16_t* out_tile_ptr(const GasCall& p, int BM, int 
 // d in [d0, world) (the put of Sections 4.1.1 and 4.2.2), and release its
 // counters there, by THREADS threads (a workgroup or one wave).  LOAD is the
 // policy of the tile's loads (coherent after a flag_wait_coherent).
-template <int BM, int BN, int THREADS, int LOAD = symtile::kLoadDefault>
+template <int BM, int BN, int THREADS, int POLICY, int LOAD = symtile::kLoadDefault>
 __device__ void put_tile_to_peers(const GasCall& p, int tm, int tn, int tid, int d0) {
     using IO = TileIO<BM, BN, THREADS>;
-    symtile::put_ranks<symtile::kStoreWriteThrough, IO::U, LOAD>(
-        out_tile_ptr(p, BM, BN, tm, tn), out_tile<BM, BN, THREADS>(p, tm, tn), p.rank, d0, p.world,
-        p.world, p.bases, tid, THREADS);
+    symtile::put_ranks<POLICY, IO::U, LOAD>(out_tile_ptr(p, BM, BN, tm, tn),
+                                            out_tile<BM, BN, THREADS>(p, tm, tn), p.rank, d0,
+                                            p.world, p.world, p.bases, tid, THREADS);
     if constexpr (THREADS > 64)
         symtile::wg_stores_done();
     else
         __builtin_amdgcn_s_waitcnt(vm_wait(0));
     if (tid < 64) {            // one wave: one release, then lane d counts slot rank + d
-        symtile::release_written_through();
+        if constexpr (POLICY == symtile::kStoreWriteThrough)
+            symtile::release_written_through();
+        else
+            symtile::fence_release<__HIP_MEMORY_SCOPE_AGENT>();
         uint32_t* flag = p.arrived + ((size_t)p.rank * p.tiles_m + tm) * p.tiles_n + tn;
         const int d = tid + d0;
         if (d < p.world)
@@ -513,7 +516,7 @@ __device__ __forceinline__ void consume_tiles_by(const GasCall& p, int cid, int 
             ok = s_ok;
         }
         if (!ok) return;
-        put_tile_to_peers<BM, BN, MOVERS, symtile::kLoadCoherent>(
+        put_tile_to_peers<BM, BN, MOVERS, symtile::kStoreWriteThrough, symtile::kLoadCoherent>(
             p, tm, tn, tid, 1 + (t + p.gemm_wgs >= p.num_tiles ? p.direct_last : p.direct_mid));
         if (tr && tid == 0) tr[SYMTILE_TRACE_COPY_DONE] = symtile::clock_now();
     }
@@ -1848,7 +1851,10 @@ __global__ __launch_bounds__(copy_threads<BM>()) void scatter_kernel(const GasPa
         uint64_t* tr = tile_trace(p, tm, tn);
         if (tr && threadIdx.x == 0)
             tr[SYMTILE_TRACE_COPY_WAIT] = tr[SYMTILE_TRACE_COPY_GO] = symtile::clock_now();
-        put_tile_to_peers<BM, BN, copy_threads<BM>()>(p, tm, tn, threadIdx.x, 1);
+        with_store_policy(p.nontemporal, [&](auto pol) {
+            put_tile_to_peers<BM, BN, copy_threads<BM>(), decltype(pol)::value>(p, tm, tn,
+                                                                                threadIdx.x, 1);
+        });
         if (tr && threadIdx.x == 0) tr[SYMTILE_TRACE_COPY_DONE] = symtile::clock_now();
     }
 }
@@ -1926,16 +1932,27 @@ constexpr int kShortK = 256;
 
 // Unsplit fused calls of up to kWriteBackTiles tiles for each rank of the world
 // write back, unless the caller asks for write-through.  A write-through store
-// is acknowledged by memory, later than by the L2, and the more slots a tile is stored to, the longer that takes, once per call; the
-// release of write-back stores walks the L2 once per tile, and an XCD's tiles
-// (one in eight) pay one after another.  Us, write-back / written through:
-// 64x64 tiles, K = 256: w = 2, 16 tiles 5.95 / 5.96, 64 tiles 6.33 / 6.03; w =
-// 8, 4 tiles 7.27 / 8.25, 64 tiles 8.11 / 8.53; K = 1024, w = 8: 8 tiles 8.6 /
-// 9.8.  K = 1024, w = 8, 64 tiles of 256x256 42.5 / 45.9, 32 of
-// 256x128 21.9 / 23.4, 32 of 128x128 15.1 / 15.4; w = 2, 64 of 256x256 31.0 /
-// 30.3.  With many tiles (fp16 8192x512x1024, w = 8): fused 121 / 69,
+// is acknowledged by memory, later than by the L2, and the more slots a tile is
+// stored to, the longer that takes, once per call; the release of write-back
+// stores walks the L2 once per tile, and an XCD's tiles (one in eight) pay one
+// after another.  Us, write-back / written through: 64x64 tiles, K = 256: w = 2,
+// 16 tiles 5.95 / 5.96, 64 tiles 6.33 / 6.03; w = 8, 4 tiles 7.27 / 8.25, 64
+// tiles 8.11 / 8.53; K = 1024, w = 8: 8 tiles 8.6 / 9.8.  K = 1024, w = 8, 64
+// tiles of 256x256 42.5 / 45.9, 32 of 256x128 21.9 / 23.4, 32 of 128x128 15.1 /
+// 15.4 (64 of them lose: K = 512 12.8 / 12.1); w = 2, 64 of 256x256 31.0 / 30.3.  With many tiles (fp16 8192x512x1024, w = 8): fused 121 / 69,
 // bulk-synchronous 157 / 74, WG_SPEC 268 / 99.
 constexpr size_t kWriteBackTiles = 8;
+// Bulk-synchronous: the longer a tile's copy to the peers (a workgroup writes 50
+// GB/s through), the more tiles.  K = 128, write-back / written through, us:
+// 256x256, w = 8 1 tile 24.1 / 30.1, 16 27.3 / 33.3, 64 32.0 / 33.5, 128 43.2 /
+// 37.1; w = 4 64 tiles 28.3 / 31.0, 128 36.6 / 35.8; w = 2 16 18.8 / 20.6, 128
+// 32.7 / 30.9; 256x224, w = 8 64 28.6 / 31.1, w = 4 32 19.4 / 20.1, 64 23.3 /
+// 22.4; 256x128, w = 8 16 15.9 / 17.5, w = 4 32 13.7 / 13.3; 128x128, w = 8 16
+// 11.4 / 11.9, 32 12.3 / 11.9; 64x64, w = 8 16 8.9 / 9.6, 64 10.1 / 10.0.
+size_t bulk_write_back_tiles(int tile_n, int world) {
+    const size_t w = world;
+    return tile_n == 256 ? std::min<size_t>(16 * w, 64) : tile_n == 224 ? 8 * w : 2 * w;
+}
 
 // waves == 0 picks the first entry of the shape (the default wave count);
 // short_k prefers the shape's build for short K, where it has one.
@@ -2231,10 +2248,14 @@ extern "C" symtile_status symtile_gemm_all_scatter(
     p.spin_limit = cfg.spin_limit;
     if (cfg.nontemporal < 0 || cfg.nontemporal > 2)
         return fail(SYMTILE_EINVAL, "nontemporal must be 0, 1 or 2");
-    p.nontemporal = cfg.nontemporal != 2 && cfg.variant == SYMTILE_FUSED_SEQ && split == 1 &&
-                            num_tiles <= kWriteBackTiles * world_size
-                        ? 0
-                        : 2;
+    size_t write_back = 0;       // tiles up to which the call writes back
+    if (cfg.nontemporal != 2 && split == 1) {
+        if (cfg.variant == SYMTILE_FUSED_SEQ)
+            write_back = kWriteBackTiles * world_size;
+        else if (cfg.variant == SYMTILE_BULK_SYNC)
+            write_back = bulk_write_back_tiles(cfg.tile_n, world_size);
+    }
+    p.nontemporal = num_tiles <= write_back ? 0 : 2;
     p.trace = cfg.trace;
     p.copy_wgs = 0;
     p.split = split;

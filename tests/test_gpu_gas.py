@@ -1039,6 +1039,34 @@ def test_slots_shared_by_producers_and_consumers(case, variant):
 
 
 @pytest.mark.parametrize("case", [
+    # world, M, N_local, tile_m, tile_n: on both sides of the tile count up to which a
+    # bulk-synchronous call writes back (2 * world; 8 * world for 256x224 tiles, 16 for 256x256)
+    (2, 64 * 4 - 3, 56, 64, 64),
+    (2, 64 * 5, 56, 64, 64),
+    (8, 128 * 4, 128 * 4, 128, 128),
+    (3, 256 * 2 + 1, 264, 256, 128),
+    (3, 256 * 2 + 1, 200, 256, 128),
+    (2, 256 * 3 + 9, 224 * 4 - 8, 256, 224),
+    (2, 256 * 4 + 9, 224 * 4 - 8, 256, 224),
+    (1, 256 * 4, 256 * 4, 256, 256),
+    (2, 256 * 8 + 1, 256 * 4 - 8, 256, 256),
+], ids=lambda c: "w%d_m%d_n%d_t%dx%d" % c)
+def test_bulk_sync_store_policies_agree_bitwise(case):
+    world, M, N, tm, tn = case
+    p = Problem(world, M, N, 72, "bf16", tm, tn, seed=M)
+    r = world - 1
+    want = {r: oracle_block(p.A, p.shards[r], "bf16")}
+    outs = []
+    for nt in (0, 1, 2, 0):
+        p.sentinel()
+        p.run(r, BULK, nontemporal=nt)
+        p.barrier()
+        check_gathered(p, want)
+        outs.append(u16(p.out.C_all()).copy())
+    assert all(np.array_equal(o, outs[0]) for o in outs)
+
+
+@pytest.mark.parametrize("case", [
     # world, M, N_local, group_m, gemm_wgs: tile rows that the swizzle groups do not divide
     (2, 64 * 9, 64 * 3, 4, 0),
     (2, 64 * 7, 64 * 5, 5, 8),
