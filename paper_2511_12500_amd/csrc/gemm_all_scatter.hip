@@ -543,15 +543,20 @@ __device__ void consume_tiles(const GasCall& p, int cid, int ncons) {
 // counters are published two intervals after the last store, when the
 // stores have been acknowledged.  Loads and stores share one in-order
 // counter, so each interval issues its load before its stores.  With fewer
-// barriers than that needs (small K) the wave stores each group as soon as
-// it is loaded.
+// barriers than that needs (K up to 4096 in 64-k stages) the wave loads eight
+// groups and stores them, so that a tile is eight waits for memory and not 64,
+// which were longer than a short K loop (bf16, us a call one group / four /
+// eight at a time: 2608x64x3712, w = 1 30.6 / 17.4 / 15.1; 8192x512x4096, w = 2
+// 94.7 / 62.3 / 58.6; 8192x2048x2048, w = 8 127 / 124 / 115; 4096x4096x3584,
+// w = 8 147 / 148 / 147).
 template <int BM, int BN>
 __device__ void copy_wave_tiles(const GasCall& p, int stages) {
     constexpr int CPR = staged_width(BN) / 8;   // 16-byte chunks per tile row
     constexpr int RPI = 64 / CPR;               // tile rows per wave-wide access
     constexpr int GROUPS = BM / RPI;
+    constexpr int FB = 8;                       // groups in flight without the pipeline
     constexpr int MAXW = SYMTILE_MAX_WORLD;
-    static_assert(64 % CPR == 0 && BM % RPI == 0 && GROUPS % 2 == 0, "copy wave split");
+    static_assert(64 % CPR == 0 && BM % RPI == 0 && GROUPS % FB == 0, "copy wave split");
     const int lane = threadIdx.x & 63;
     const int G = p.gemm_wgs;
     const int intervals = stages + 3;
@@ -625,8 +630,14 @@ __device__ void copy_wave_tiles(const GasCall& p, int stages) {
             const int per = (GROUPS + intervals - 1) / intervals;
             for (int b = 0; b < intervals; ++b) {
                 if (!published) {
-                    for (int q = 0; q < per && g < GROUPS; ++q, ++g)
-                        store_group(symtile::buf_ld16(rs, voff, (uint32_t)g * group_bytes), g);
+                    for (int q = 0; q < per && g < GROUPS; q += FB, g += FB) {
+                        symtile::u32x4 v[FB];
+#pragma unroll
+                        for (int i = 0; i < FB; ++i)
+                            v[i] = symtile::buf_ld16(rs, voff, (uint32_t)(g + i) * group_bytes);
+#pragma unroll
+                        for (int i = 0; i < FB; ++i) store_group(v[i], g + i);
+                    }
                     if (g == GROUPS) {
                         publish();
                         published = true;

@@ -607,6 +607,9 @@ WAVESPEC = 4
     (8, 1024, 1024, 4096, 8, "bf16"),      # 32 tiles, 4 per workgroup
     (4, 600, 520, 264, 3, "bf16"),         # ragged rows, columns and K; 5 tiles each
     (2, 257, 136, 72, 1, "f16"),           # one workgroup, every tile through the copy wave
+    (2, 520, 264, 4160, 2, "bf16"),        # K from which the copy wave runs its pipeline
+    (5, 500, 392, 648, 2, "f16"),          # several groups a barrier, ragged rows
+    (1, 520, 264, 64, 2, "bf16"),          # no other slot, one stage
 ], ids=lambda c: "w%d_m%d_n%d_k%d_g%d_%s" % c)
 def test_wave_spec_matches_fused_bitwise(case):
     """Section 4.2.3: compute waves store each tile locally and one extra wave
