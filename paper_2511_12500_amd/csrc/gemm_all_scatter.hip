@@ -283,10 +283,16 @@ __device__ __forceinline__ int swz_b(int k) {
 // remap makes consecutive units land on one XCD, and the slices of a tile are
 // consecutive units, so with split-K they share that XCD's L2 (and the
 // partial tiles they exchange stay there).  Where the slices exchange nothing
-// (the reduction-kernel mode) consecutive units are the tiles of one slice
-// instead, so that an XCD reads a part of K of all its panels (128x128 tiles, 1024x4096x1024 in 4 slices: 3 MiB of A and
-// B per XCD, which its L2 holds, instead of 6; 26.9 -> 25.0 us a call; 64x8192x3584
-// 22.2 -> 21.4).  Without split-K a unit is a tile.
+// (the reduction-kernel mode) and are long, consecutive units are the tiles of
+// one slice instead, so that an XCD reads a part of K of all its panels.  With
+// shorter slices that is no gain, and with 128 units and more of 128x128 tiles
+// and larger the partials of the XCDs' slices, stored all at once, take up to
+// 10 us longer (w = 8, us a call slice / tile after slice: 64x8192x3584, 64x64
+// tiles, 4 slices 21.4 / 21.1; 512x8192x512, 64x64, 4 19.6 / 18.8;
+// 1024x8192x1024, 128x128, 4 34.1 / 33.0; 1024x4096x1024 26.0 / 26.4;
+// 1024x2896x1024 23.4 / 26.8; 1024x2048x1024, 256x256, 8 30.4 / 41.2;
+// 512x2896x1280, 256x128, 8 24.0 / 35.0).  Without split-K a unit is a tile.
+constexpr int kSliceMajorK = 2048;          // k per slice
 __device__ __forceinline__ void unit_coords(int u, int G, const GasCall& p, int& tm, int& tn,
                                             int& s) {
     int L = u;
@@ -296,7 +302,7 @@ __device__ __forceinline__ void unit_coords(int u, int G, const GasCall& p, int&
         L = round * G + (pos & 7) * (G >> 3) + (pos >> 3);
     }
     if (p.split > 1) {
-        if (p.sk_band == 2) {
+        if (p.sk_band == 2 && p.K / kSliceMajorK >= p.split) {
             s = p.by_tiles(L);
             L -= s * p.num_tiles;
         } else {
