@@ -104,6 +104,7 @@ struct GasCall {
     // slice to arrive sums and stores the whole tile; 2 = every slice only
     // writes its partial (the first kernel of the reduction-kernel mode).
     int sk_band;
+    int slice_major;        // order of the work units, see unit_coords
     // WG_SPEC and UNFUSED_PC: how many of the world - 1 other slots a producer
     // stores itself, of its last tile and of the tiles before it; the
     // consumers put the others.
@@ -132,7 +133,8 @@ struct GasParams {
     uint32_t who;           // rank, world, role, nontemporal, sk_band: 4 bits each; split: 8
     uint32_t shifts;        // of by_wgs, by_width, by_rows, by_last_rows
     uint32_t mul_last_rows, mul_split;
-    uint32_t share;         // direct_last, direct_mid, reduce_all: 4 bits each; reduce_bands: 8
+    uint32_t share;         // direct_last, direct_mid, reduce_all: 4 bits each; reduce_bands: 8;
+                            // slice_major: 1
     uint32_t shifts2;       // of by_split, by_tiles_n, by_tiles
     uint16_t* C;
     uint32_t* arrived;
@@ -161,7 +163,8 @@ GasParams pack(const GasCall& c) {
     a.shifts = c.by_wgs.sh | c.by_width.sh << 8 | c.by_rows.sh << 16 | c.by_last_rows.sh << 24;
     a.shifts2 = c.by_split.sh | c.by_tiles_n.sh << 8 | c.by_tiles.sh << 16;
     a.share = (uint32_t)c.direct_last | (uint32_t)c.direct_mid << 4 |
-              (uint32_t)c.reduce_all << 8 | (uint32_t)c.reduce_bands << 12;
+              (uint32_t)c.reduce_all << 8 | (uint32_t)c.reduce_bands << 12 |
+              (uint32_t)c.slice_major << 20;
     a.arrived = c.arrived, a.bases = c.bases, a.trace = c.trace, a.sk_cnt = c.sk_cnt;
     a.err = c.err, a.ready = c.ready, a.epoch = c.epoch, a.spin_limit = c.spin_limit;
     a.copy_wgs = c.copy_wgs;
@@ -182,6 +185,7 @@ __device__ __forceinline__ GasCall unpack(const GasParams& a) {
     c.nontemporal = a.who >> 12 & 15, c.sk_band = a.who >> 16 & 15, c.split = a.who >> 20 & 255;
     c.direct_last = a.share & 15, c.direct_mid = a.share >> 4 & 15;
     c.reduce_all = a.share >> 8 & 15, c.reduce_bands = a.share >> 12 & 255;
+    c.slice_major = a.share >> 20 & 1;
     c.by_wgs = Div{a.mul_wgs, a.shifts & 255};
     c.by_width = Div{a.mul_width, a.shifts >> 8 & 255};
     c.by_rows = Div{a.mul_rows, a.shifts >> 16 & 255};
@@ -205,7 +209,7 @@ __device__ __forceinline__ GasCall unpack(const GasParams& a) {
 __device__ __forceinline__ GasCall unpack_unsplit(const GasParams& a) {
     GasCall c = unpack(a);
     c.split = 1;
-    c.sk_band = 0;
+    c.sk_band = c.slice_major = 0;
     c.by_split = Div{1u << 31, 0};
     c.units = c.num_tiles;
     return c;
@@ -282,17 +286,10 @@ __device__ __forceinline__ int swz_b(int k) {
 // Producer-order work unit u -> (tile row, tile column, K slice).  The XCD
 // remap makes consecutive units land on one XCD, and the slices of a tile are
 // consecutive units, so with split-K they share that XCD's L2 (and the
-// partial tiles they exchange stay there).  Where the slices exchange nothing
-// (the reduction-kernel mode) and are long, consecutive units are the tiles of
-// one slice instead, so that an XCD reads a part of K of all its panels.  With
-// shorter slices that is no gain, and with 128 units and more of 128x128 tiles
-// and larger the partials of the XCDs' slices, stored all at once, take up to
-// 10 us longer (w = 8, us a call slice / tile after slice: 64x8192x3584, 64x64
-// tiles, 4 slices 21.4 / 21.1; 512x8192x512, 64x64, 4 19.6 / 18.8;
-// 1024x8192x1024, 128x128, 4 34.1 / 33.0; 1024x4096x1024 26.0 / 26.4;
-// 1024x2896x1024 23.4 / 26.8; 1024x2048x1024, 256x256, 8 30.4 / 41.2;
-// 512x2896x1280, 256x128, 8 24.0 / 35.0).  Without split-K a unit is a tile.
-constexpr int kSliceMajorK = 2048;          // k per slice
+// partial tiles they exchange stay there).  With slice_major (see the rule at
+// slice_major_units) consecutive units are the tiles of one slice instead, so
+// that an XCD reads a part of K of all its panels.  Without split-K a unit is a
+// tile.
 __device__ __forceinline__ void unit_coords(int u, int G, const GasCall& p, int& tm, int& tn,
                                             int& s) {
     int L = u;
@@ -302,7 +299,7 @@ __device__ __forceinline__ void unit_coords(int u, int G, const GasCall& p, int&
         L = round * G + (pos & 7) * (G >> 3) + (pos >> 3);
     }
     if (p.split > 1) {
-        if (p.sk_band == 2 && p.K / kSliceMajorK >= p.split) {
+        if (p.slice_major) {
             s = p.by_tiles(L);
             L -= s * p.num_tiles;
         } else {
@@ -2054,6 +2051,24 @@ void share_slots(GasCall& p, int bm, int bn, int g, int c) {
     }
 }
 
+// Reduction-kernel mode: whether an XCD takes the tiles of one K slice rather than
+// the slices of a tile, which exchange nothing there.  It does where the slices
+// are long, or the units fill the chip and give a CU 1024 k or more: the XCD's
+// L2 then reads a part of K of the panels only.  Otherwise the order is no gain,
+// and the steady-state first kernel takes up to 10 us longer with 64 units and
+// more of 128x128 tiles and larger (us a call, slices of a tile / of one K slice,
+// w = 8 unless given: 64x8192x3584, 64x64 tiles, 4 slices 21.4 / 21.1;
+// 512x8192x512, 64x64, 4 19.6 / 18.8; 1024x8192x1024, 128x128, 4 34.1 / 33.0;
+// 2048x4096x1024, 256x128, 4 39.0 / 37.6; bf16 1024x4096x1024, 128x128, 4 25.0 /
+// 24.4; 1024x2896x1024 23.4 / 26.8; 1024x2048x1024, 256x256, 8 30.4 / 41.2;
+// 512x2896x1280, 256x128, 8 24.0 / 35.0; over 2600 calls of 24 to 768 units the
+// rule's choice is 0.5% above the better of the two, the worst 1% 7% and more).
+bool slice_major_units(int K, int tiles, int split) {
+    constexpr int kUnits = 256;             // about the CUs
+    return K / 2048 >= split ||
+           ((int64_t)tiles * split >= kUnits && (int64_t)K * tiles >= 1024 * kUnits);
+}
+
 // The divisors of a call, once everything else is set.
 void set_divs(GasCall& p) {
     p.by_wgs = make_div(p.gemm_wgs);
@@ -2293,7 +2308,7 @@ extern "C" symtile_status symtile_gemm_all_scatter(
     } restore{prev};
 
     const int ntiles = (int)num_tiles;
-    p.sk_band = 0;
+    p.sk_band = p.slice_major = 0;
     p.direct_last = p.direct_mid = 0;
     p.reduce_bands = 1;
     p.reduce_all = 0;
@@ -2328,6 +2343,7 @@ extern "C" symtile_status symtile_gemm_all_scatter(
                 (p.sk_band == 1 && g > cus))
                 p.sk_band = 2;
         }
+        p.slice_major = p.sk_band == 2 && slice_major_units(K, ntiles, split);
         p.role = cfg.variant == SYMTILE_FUSED_SEQ ? ROLE_FUSED : ROLE_LOCAL_ONLY;
         set_divs(p);
         GasParams packed = pack(p);

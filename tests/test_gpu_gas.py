@@ -768,6 +768,7 @@ def test_banded_split_reduce_matches_last_arriver_bitwise(case):
     (2, 70, 72, 2048, 64, 64, "f16", 64),
     (2, 2048, 2048, 96, 64, 64, "f16", 3),     # 1024 tiles: reduction units past the CU count
     (2, 136, 200, 6152, 64, 64, "bf16", 3),    # slices long enough to be an XCD's own
+    (2, 1024, 496, 2056, 64, 64, "f16", 2),    # ... with 256 units and 1028 k for each
 ], ids=lambda c: "w%d_m%d_n%d_k%d_t%dx%d_%s_s%d" % c)
 @pytest.mark.parametrize("variant", [FUSED, BULK], ids=VNAMES.get)
 def test_reduction_kernel_matches_last_arriver_bitwise(case, variant):
