@@ -1962,7 +1962,11 @@ constexpr size_t kWriteBackTiles = 8;
 // 37.1; w = 4 64 tiles 28.3 / 31.0, 128 36.6 / 35.8; w = 2 16 18.8 / 20.6, 128
 // 32.7 / 30.9; 256x224, w = 8 64 28.6 / 31.1, w = 4 32 19.4 / 20.1, 64 23.3 /
 // 22.4; 256x128, w = 8 16 15.9 / 17.5, w = 4 32 13.7 / 13.3; 128x128, w = 8 16
-// 11.4 / 11.9, 32 12.3 / 11.9; 64x64, w = 8 16 8.9 / 9.6, 64 10.1 / 10.0.
+// 11.4 / 11.9, 32 12.3 / 11.9; 64x64, w = 8 16 8.9 / 9.6, 64 10.1 / 10.0.  With
+// split-K the copy kernel follows the same rule, and so does a last arriver,
+// which stores whole tiles by itself (fused, K = 1024, 2 slices, w = 8, write-back
+// over written through: 256x256 4 tiles 0.91, 32 0.94; 256x128 16 0.97; 128x128 16
+// 0.97, 64 1.08; 64x64 16 0.92, 64 1.02).
 size_t bulk_write_back_tiles(int tile_n, int world) {
     const size_t w = world;
     return tile_n == 256 ? std::min<size_t>(16 * w, 64) : tile_n == 224 ? 8 * w : 2 * w;
@@ -2281,13 +2285,14 @@ extern "C" symtile_status symtile_gemm_all_scatter(
     if (cfg.nontemporal < 0 || cfg.nontemporal > 2)
         return fail(SYMTILE_EINVAL, "nontemporal must be 0, 1 or 2");
     size_t write_back = 0;       // tiles up to which the call writes back
-    if (cfg.nontemporal != 2 && split == 1) {
-        if (cfg.variant == SYMTILE_FUSED_SEQ)
+    if (cfg.nontemporal != 2) {
+        if (cfg.variant == SYMTILE_FUSED_SEQ && split == 1)
             write_back = kWriteBackTiles * world_size;
-        else if (cfg.variant == SYMTILE_BULK_SYNC)
+        else if (cfg.variant == SYMTILE_FUSED_SEQ || cfg.variant == SYMTILE_BULK_SYNC)
             write_back = bulk_write_back_tiles(cfg.tile_n, world_size);
     }
-    p.nontemporal = num_tiles <= write_back ? 0 : 2;
+    const int policy = num_tiles <= write_back ? 0 : 2;
+    p.nontemporal = split == 1 ? policy : 2;
     p.trace = cfg.trace;
     p.copy_wgs = 0;
     p.split = split;
@@ -2342,6 +2347,8 @@ extern "C" symtile_status symtile_gemm_all_scatter(
             if (cfg.split_reduce == SYMTILE_SPLIT_REDUCE_KERNEL || (automatic && split > 2) ||
                 (p.sk_band == 1 && g > cus))
                 p.sk_band = 2;
+            // (the other reductions' bands are published written through)
+            if (p.sk_band == 0) p.nontemporal = policy;
         }
         p.slice_major = p.sk_band == 2 && slice_major_units(K, ntiles, split);
         p.role = cfg.variant == SYMTILE_FUSED_SEQ ? ROLE_FUSED : ROLE_LOCAL_ONLY;
@@ -2376,6 +2383,8 @@ extern "C" symtile_status symtile_gemm_all_scatter(
             int c = cfg.copy_wgs > 0 ? cfg.copy_wgs : cus * (1024 / v->copy_threads);
             c = std::min(c, ntiles);
             p.copy_wgs = c;
+            p.nontemporal = policy;
+            packed = pack(p);
             SYMTILE_HIP(hipLaunchKernel(v->scatter, dim3(c), dim3(v->copy_threads), args, 0, stream));
         }
         return SYMTILE_OK;

@@ -1045,7 +1045,7 @@ def test_slots_shared_by_producers_and_consumers(case, variant):
 
 @pytest.mark.parametrize("case", [
     # world, M, N_local, tile_m, tile_n: on both sides of the tile count up to which a
-    # bulk-synchronous call writes back (2 * world; 8 * world for 256x224 tiles, 16 for 256x256)
+    # call writes back (2 * world; 8 * world for 256x224 tiles, 16 for 256x256)
     (2, 64 * 4 - 3, 56, 64, 64),
     (2, 64 * 5, 56, 64, 64),
     (8, 128 * 4, 128 * 4, 128, 128),
@@ -1056,18 +1056,25 @@ def test_slots_shared_by_producers_and_consumers(case, variant):
     (1, 256 * 4, 256 * 4, 256, 256),
     (2, 256 * 8 + 1, 256 * 4 - 8, 256, 256),
 ], ids=lambda c: "w%d_m%d_n%d_t%dx%d" % c)
-def test_bulk_sync_store_policies_agree_bitwise(case):
+@pytest.mark.parametrize("split", [0, 2], ids=["unsplit", "split2"])
+def test_store_policies_agree_bitwise(case, split):
+    """Bulk-synchronous calls, and with split-K every reduction and the fused last arriver."""
     world, M, N, tm, tn = case
+    pkg = sym()
     p = Problem(world, M, N, 72, "bf16", tm, tn, seed=M)
     r = world - 1
-    want = {r: oracle_block(p.A, p.shards[r], "bf16")}
+    want = {r: oracle_block_bounded(p.A, p.shards[r], "bf16")}
+    modes = [(BULK, 0)] if not split else [(BULK, pkg.SPLIT_REDUCE_LAST), (FUSED, pkg.SPLIT_REDUCE_LAST),
+                                           (BULK, pkg.SPLIT_REDUCE_AUTO),
+                                           (BULK, pkg.SPLIT_REDUCE_KERNEL)]
     outs = []
-    for nt in (0, 1, 2, 0):
-        p.sentinel()
-        p.run(r, BULK, nontemporal=nt)
-        p.barrier()
-        check_gathered(p, want)
-        outs.append(u16(p.out.C_all()).copy())
+    for variant, red in modes:
+        for nt in (0, 1, 2, 0):
+            p.sentinel()
+            p.run(r, variant, nontemporal=nt, split_k=split, split_reduce=red)
+            p.barrier()
+            check_gathered(p, want)
+            outs.append(u16(p.out.C_all()).copy())
     assert all(np.array_equal(o, outs[0]) for o in outs)
 
 
