@@ -111,6 +111,8 @@ def parse_args(argv=None):
                     help="minimum length of each leg's clock-settling phase")
     ap.add_argument("--settle-launches", type=int, default=100,
                     help="minimum launches of each leg's clock-settling phase")
+    ap.add_argument("--detail", action="store_true",
+                    help="print every field of every configuration (a line of some 20 KB)")
     ap.add_argument("--no-sweep", action="store_true",
                     help="only the headline legs (no configs array, no per-config oracle)")
     ap.add_argument("--sweep-steps", type=int, default=20, help="timed launches per configs entry")
@@ -646,6 +648,34 @@ def cpu_baseline(args, wl, A, B, workload):
                       f"counters, {done} repetitions, {total:.1f} s"}
 
 
+def compact(line: dict) -> dict:
+    """The line at a size that logs keep whole (under 8 KB): five significant
+    digits, and of every swept configuration what identifies it, its time, its
+    rate and the fraction of its roofline (--detail prints everything)."""
+    def short(x):
+        if isinstance(x, float):
+            return float("%.5g" % x)
+        if isinstance(x, dict):
+            return {k: short(v) for k, v in x.items()}
+        return [short(v) for v in x] if isinstance(x, list) else x
+
+    keep = ("workload", "schedule", "tile", "split_k", "split_reduce", "gemm_wgs", "copy_wgs",
+            "waves", "graph_calls", "ms", "cold_ms", "warm_ms", "value", "unit")
+    out = short(line)
+    # the headline numbers keep every digit
+    out.update({k: line[k] for k in ("value", "ms_per_step", "vs_baseline") if k in line})
+    if "configs" in out:
+        out["configs"] = [dict({k: c[k] for k in keep if c.get(k) not in (None, 0)},
+                               frac=c["roofline"]["frac"]) for c in out["configs"]]
+        for c in out["configs"]:
+            if c.get("split_k") == 1:
+                del c["split_k"]
+    if "cpu_configs" in out:
+        out["cpu_configs"] = {k: v["value"] if isinstance(v, dict) else v
+                              for k, v in out["cpu_configs"].items()}
+    return out
+
+
 def main(argv=None):
     args = parse_args(argv)
     if args.oracle_time:                  # child of oracle_time_child: CPU only
@@ -720,7 +750,7 @@ def main(argv=None):
         for _ in range(3):
             y.copy_(x)
         torch.cuda.synchronize()
-    print(json.dumps(line), flush=True)
+    print(json.dumps(line if args.detail else compact(line), separators=(",", ":")), flush=True)
     return 0
 
 
