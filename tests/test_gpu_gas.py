@@ -504,8 +504,9 @@ def test_split_k_timeout_then_stale_workspace_is_reported(mode, again):
                                   (8, 1024, 1024, 4096, 128, 128, "f16")],
                          ids=lambda c: "w%d_m%d_n%d_k%d_t%dx%d_%s" % c)
 def test_four_and_eight_wave_kernels_agree_bitwise(case):
-    """Both wave layouts compute each accumulator in the same order, so the
-    heaps they leave are identical; both match the oracle."""
+    """Both wave counts a caller may ask for leave identical heaps that match the
+    oracle.  256x256 tiles have a build for each, which compute each accumulator
+    in the same order; the other tiles run their one build for both."""
     world, M, N, K, tm, tn, dtype = case
     p = Problem(world, M, N, K, dtype, tm, tn, seed=5)
     want = {1 % world: oracle_block(p.A, p.shards[1 % world], dtype)}
@@ -734,7 +735,7 @@ BANDED = [
     (3, 1000, 520, 1000, 128, 128, "f16", 4),    # 32-row bands; the last tile row ragged
     (4, 130, 264, 520, 256, 256, "bf16", 8),     # large accumulators: own rows via memory
     (3, 300, 504, 200, 256, 224, "bf16", 2),     # 16x16x32 MFMA tile, 128-row bands
-    (2, 200, 72, 96, 64, 64, "f16", 2),          # 64x64 tile (4 waves), 32-row bands
+    (2, 200, 72, 96, 64, 64, "f16", 2),          # 64x64 tile, 32-row bands
     (2, 512, 512, 2048, 256, 256, "f16", 2),     # large accumulators, two slices
 ]
 
