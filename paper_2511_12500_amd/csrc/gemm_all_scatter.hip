@@ -121,9 +121,9 @@ struct GasCall {
 // needs before its first loads lies in the first 128.  Kernel arguments are in
 // host memory, and each 64-byte line of them that a workgroup touches is a
 // round trip there (back-to-back calls, us, with the 232 bytes of GasCall ->
-// now: 500x256x2048 in 64x64 tiles 7.6 -> 7.0, tiny two-rank call 5.8 -> 5.3,
-// 64x8192x3584 in 4 slices 22.9 -> 22.1).  Everything that follows from other fields is left out,
-// small fields share words.
+// now: 500x256x2048 in 64x64 tiles 7.6 -> 7.0, 64x8192x3584 in 4 slices 22.9 ->
+// 22.1; the tiny two-rank call, which waits for the host, 5.6 both).  Everything
+// that follows from other fields is left out, small fields share words.
 struct GasParams {
     const uint16_t* A;
     const uint16_t* B;
@@ -146,7 +146,7 @@ struct GasParams {
     uint32_t* ready;
     uint32_t epoch, spin_limit;
     int copy_wgs;
-    uint32_t mul_tiles_n, mul_tiles, reserved;
+    uint32_t mul_tiles_n, mul_tiles, pad;
 };
 static_assert(sizeof(GasParams) == 168, "kernel arguments");
 
@@ -671,9 +671,9 @@ __device__ void copy_wave_tiles(const GasCall& p, int stages) {
 // share each SIMD, so one wave's MFMAs run while the other waits on LDS,
 // global loads or the barrier.
 //
-// Loop of a tile shape.  Tiles up to 256 x 128 run a deep loop: stages of 64 or 128 k (A rows as whole 128-byte lines), one
-// barrier per stage, loads two or three stages ahead.  What bounds the small
-// tiles is not the matrix cores but the fixed cost of a stage (barrier, LDS
+// Loop of a tile shape.  Tiles up to 256 x 128 run a deep loop: stages of 64 or
+// 128 k (A rows as whole 128-byte lines), one barrier per stage, loads two or
+// three stages ahead.  What bounds the small tiles is not the matrix cores but the fixed cost of a stage (barrier, LDS
 // latency, issue; some 270 cycles with nothing else in it) and the loads in
 // flight, so a stage carries as much k as the LDS allows, and its code has no
 // branch.  64 x 64 tiles also split each stage's k between two groups of four
@@ -729,6 +729,9 @@ __device__ __forceinline__ void gas_body(const GasCall& p) {
     constexpr int RING = DEEP ? LC.ns * DSTAGE : NS * STAGE;
     // the K groups' exchange lies behind the ring, so it needs no barrier before it
     constexpr int X_BYTES = KG > 1 ? BM * BN * 4 : 0;
+    // (The reduction kernel stages one output tile only; allocating just that
+    // measures the same, us a call: 64x8192x3584, 4 slices 21.1 either way,
+    // 1024x4096x1024 26.2 / 26.3.)
     constexpr int LDS_BYTES = (RING > C_BYTES ? RING : C_BYTES) + X_BYTES;
     constexpr int A_RPI = 1024 / kRowBytes;     // A rows per 1 KiB direct-to-LDS load
     constexpr int A_INSTR = BM / A_RPI / NW;    // direct-to-LDS A loads per wave per stage
@@ -1645,11 +1648,11 @@ __device__ __forceinline__ void gas_body(const GasCall& p) {
                     for (int q = 0; q < ks; q += QB)
                         add_partial(tmp, q, min(QB, ks - q), q == 0);
                     if (ks > 0) {
-    #pragma unroll
+#pragma unroll
                         for (int i = 0; i < MI; ++i)
-    #pragma unroll
+#pragma unroll
                             for (int j = 0; j < NI; ++j)
-    #pragma unroll
+#pragma unroll
                                 for (int e = 0; e < ACC_N; ++e)
                                     if (covered(i, true)) acc[i][j][e] = tmp[i][j][e] + acc[i][j][e];
                     }
@@ -1775,10 +1778,8 @@ __device__ __forceinline__ void gas_body(const GasCall& p) {
                     u = __shfl(u, 0);
                     const uint32_t w1 = __shfl(red_cnt1, 0);
                     publish = w1 == 0 && u == (uint32_t)p.reduce_bands - 1u;
-                    if (publish) {
-                            if (tid == 0)
-                            symtile::atomic_xchg<__ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT>(cnt, 0u);
-                    }
+                    if (publish && tid == 0)
+                        symtile::atomic_xchg<__ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT>(cnt, 0u);
                 } else if (banded) {
                     // Banded: the tile is whole once every slice has stored its
                     // band.  Each slice releases its stores and takes a second
@@ -1794,10 +1795,9 @@ __device__ __forceinline__ void gas_body(const GasCall& p) {
                     u2 = __shfl(u2, 0);
                     publish = u2 == 2u * (uint32_t)p.split - 1u;
                     if (publish) {
-                        // the other slices' band stores happen before the counters
-                        // move: written through, they were in memory before their
-                        // slices' tickets; otherwise acquire their releases
-                            if (tid == 0) {
+                        // the other slices' band stores, written through, were in
+                        // memory before their slices' tickets
+                        if (tid == 0) {
                             symtile::atomic_xchg<__ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT>(cnt, 0u);
                             symtile::atomic_xchg<__ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT>(cnt + 1, 0u);
                         }
