@@ -689,7 +689,9 @@ __device__ void copy_wave_tiles(const GasCall& p, int stages) {
 // tiles for K up to kShortK, where its small first stage starts the MFMAs
 // sooner than a deep one and there are few stages to save on (K = 256: 500 x
 // 2048 in 64 x 64 tiles 7.1 against 7.4 us, 1400 x 512 in 128 x 128 tiles 7.0
-// against 7.4; K = 512: 9.0 against 8.8 for the latter).
+// against 7.4; K = 512: 9.0 against 8.8 for the latter; whole builds, the one
+// before the deep loop against this: K = 264 6.4 and 6.3, 7.8 and 7.4, K = 384 6.9
+// and 6.3, K = 512 7.6 and 6.7, 9.6 and 8.6).
 struct LoopCfg {
     int kg, bk, ns;         // K groups (0: the 32-k ring), k per stage, LDS slots
     int wgm, wgn;           // waves down and across the tile after the K loop
