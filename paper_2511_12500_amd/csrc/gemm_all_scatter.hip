@@ -673,25 +673,25 @@ __device__ void copy_wave_tiles(const GasCall& p, int stages) {
 //
 // Loop of a tile shape.  Tiles up to 256 x 128 run a deep loop: stages of 64 or
 // 128 k (A rows as whole 128-byte lines), one barrier per stage, loads two or
-// three stages ahead.  What bounds the small tiles is not the matrix cores but the fixed cost of a stage (barrier, LDS
-// latency, issue; some 270 cycles with nothing else in it) and the loads in
-// flight, so a stage carries as much k as the LDS allows, and its code has no
-// branch.  64 x 64 tiles also split each stage's k between two groups of four
-// waves: a wave then holds a square block, which cuts the fragment reads per
-// MFMA by a third against eight waves side by side, and the groups' sums meet
-// once per tile through LDS.  K loop per 64 k on full chips (w = 1, 32-k ring
-// before -> now): 64 x 64 0.366 -> 0.196 us, 128 x 128 0.635 -> 0.541, 256 x
-// 128 1.011 -> 0.875.  Two groups on 128 x 128 reach 0.509, but the exchange
-// costs 0.6 us a tile: calls with 8 to 64 stages are faster without (1400 x
-// 1024 x 512 12.5 against 12.0 us).  64 x 64 with one group: 0.219.
-// Fragments read two steps ahead instead of one: no gain.  256-wide tiles
-// have no LDS for three 64-k stages and keep the ring, and so do the smaller
-// tiles for K up to kShortK, where its small first stage starts the MFMAs
-// sooner than a deep one and there are few stages to save on (K = 256: 500 x
-// 2048 in 64 x 64 tiles 7.1 against 7.4 us, 1400 x 512 in 128 x 128 tiles 7.0
-// against 7.4; K = 512: 9.0 against 8.8 for the latter; whole builds, the one
-// before the deep loop against this: K = 264 6.4 and 6.3, 7.8 and 7.4, K = 384 6.9
-// and 6.3, K = 512 7.6 and 6.7, 9.6 and 8.6).
+// three stages ahead.  What bounds the small tiles is not the matrix cores but
+// the fixed cost of a stage (barrier, LDS latency, issue; some 270 cycles with
+// nothing else in it) and the loads in flight, so a stage carries as much k as
+// the LDS allows, and its code has no branch.  64 x 64 tiles also split each
+// stage's k between two groups of four waves: a wave then holds a square block,
+// which cuts the fragment reads per MFMA by a third against eight waves side by
+// side, and the groups' sums meet once per tile through LDS.  K loop per 64 k
+// on full chips (w = 1, 32-k ring before -> now): 64 x 64 0.366 -> 0.196 us,
+// 128 x 128 0.635 -> 0.541, 256 x 128 1.011 -> 0.875.  Two groups on 128 x 128
+// reach 0.509, but the exchange costs 0.6 us a tile: calls with 8 to 64 stages
+// are faster without (1400 x 1024 x 512 12.5 against 12.0 us).  64 x 64 with
+// one group: 0.219. Fragments read two steps ahead instead of one: no gain.
+// 256-wide tiles have no LDS for three 64-k stages and keep the ring, and so do
+// the smaller tiles for K up to kShortK, where its small first stage starts the
+// MFMAs sooner than a deep one and there are few stages to save on (K = 256:
+// 500 x 2048 in 64 x 64 tiles 7.1 against 7.4 us, 1400 x 512 in 128 x 128 tiles
+// 7.0 against 7.4; K = 512: 9.0 against 8.8 for the latter; whole builds, the
+// one before the deep loop against this: K = 264 6.4 and 6.3, 7.8 and 7.4, K =
+// 384 6.9 and 6.3, K = 512 7.6 and 6.7, 9.6 and 8.6).
 struct LoopCfg {
     int kg, bk, ns;         // K groups (0: the 32-k ring), k per stage, LDS slots
     int wgm, wgn;           // waves down and across the tile after the K loop
@@ -1951,11 +1951,12 @@ constexpr int kShortK = 256;
 // is acknowledged by memory, later than by the L2, and the more slots a tile is
 // stored to, the longer that takes, once per call; the release of write-back
 // stores walks the L2 once per tile, and an XCD's tiles (one in eight) pay one
-// after another.  Us, write-back / written through: 64x64 tiles, K = 256: w = 2,
-// 16 tiles 5.95 / 5.96, 64 tiles 6.33 / 6.03; w = 8, 4 tiles 7.27 / 8.25, 64
+// after another.  Us, write-back / written through: 64x64 tiles, K = 256: w =
+// 2, 16 tiles 5.95 / 5.96, 64 tiles 6.33 / 6.03; w = 8, 4 tiles 7.27 / 8.25, 64
 // tiles 8.11 / 8.53; K = 1024, w = 8: 8 tiles 8.6 / 9.8.  K = 1024, w = 8, 64
 // tiles of 256x256 42.5 / 45.9, 32 of 256x128 21.9 / 23.4, 32 of 128x128 15.1 /
-// 15.4 (64 of them lose: K = 512 12.8 / 12.1); w = 2, 64 of 256x256 31.0 / 30.3.  With many tiles (fp16 8192x512x1024, w = 8): fused 121 / 69,
+// 15.4 (64 of them lose: K = 512 12.8 / 12.1); w = 2, 64 of 256x256 31.0 /
+// 30.3.  With many tiles (fp16 8192x512x1024, w = 8): fused 121 / 69,
 // bulk-synchronous 157 / 74, WG_SPEC 268 / 99.
 constexpr size_t kWriteBackTiles = 8;
 // Bulk-synchronous: the longer a tile's copy to the peers (a workgroup writes 50
