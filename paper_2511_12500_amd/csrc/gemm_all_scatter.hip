@@ -1955,7 +1955,7 @@ constexpr int kShortK = 256;
 // 2, 16 tiles 5.95 / 5.96, 64 tiles 6.33 / 6.03; w = 8, 4 tiles 7.27 / 8.25, 64
 // tiles 8.11 / 8.53; K = 1024, w = 8: 8 tiles 8.6 / 9.8.  K = 1024, w = 8, 64
 // tiles of 256x256 42.5 / 45.9, 32 of 256x128 21.9 / 23.4, 32 of 128x128 15.1 /
-// 15.4 (64 of them lose: K = 512 12.8 / 12.1); w = 2, 64 of 256x256 31.0 /
+// 15.4 (64 of them lose, K = 512 12.8 / 12.1, so they stop at half); w = 2, 64 of 256x256 31.0 /
 // 30.3.  With many tiles (fp16 8192x512x1024, w = 8): fused 121 / 69,
 // bulk-synchronous 157 / 74, WG_SPEC 268 / 99.
 constexpr size_t kWriteBackTiles = 8;
@@ -2290,7 +2290,8 @@ extern "C" symtile_status symtile_gemm_all_scatter(
     size_t write_back = 0;       // tiles up to which the call writes back
     if (cfg.nontemporal != 2) {
         if (cfg.variant == SYMTILE_FUSED_SEQ && split == 1)
-            write_back = kWriteBackTiles * world_size;
+            write_back = (cfg.tile_n == 128 && cfg.tile_m == 128 ? kWriteBackTiles / 2
+                                                                 : kWriteBackTiles) * world_size;
         else if (cfg.variant == SYMTILE_FUSED_SEQ || cfg.variant == SYMTILE_BULK_SYNC)
             write_back = bulk_write_back_tiles(cfg.tile_n, world_size);
     }

@@ -1050,6 +1050,7 @@ def test_slots_shared_by_producers_and_consumers(case, variant):
     (2, 64 * 4 - 3, 56, 64, 64),
     (2, 64 * 5, 56, 64, 64),
     (8, 128 * 4, 128 * 4, 128, 128),
+    (2, 128 * 3, 128 * 3 - 8, 128, 128),       # fused: 4 * world
     (3, 256 * 2 + 1, 264, 256, 128),
     (3, 256 * 2 + 1, 200, 256, 128),
     (2, 256 * 3 + 9, 224 * 4 - 8, 256, 224),
@@ -1059,13 +1060,14 @@ def test_slots_shared_by_producers_and_consumers(case, variant):
 ], ids=lambda c: "w%d_m%d_n%d_t%dx%d" % c)
 @pytest.mark.parametrize("split", [0, 2], ids=["unsplit", "split2"])
 def test_store_policies_agree_bitwise(case, split):
-    """Bulk-synchronous calls, and with split-K every reduction and the fused last arriver."""
+    """Bulk-synchronous and fused calls, and with split-K every reduction and the fused
+    last arriver."""
     world, M, N, tm, tn = case
     pkg = sym()
     p = Problem(world, M, N, 72, "bf16", tm, tn, seed=M)
     r = world - 1
     want = {r: oracle_block_bounded(p.A, p.shards[r], "bf16")}
-    modes = [(BULK, 0)] if not split else [(BULK, pkg.SPLIT_REDUCE_LAST), (FUSED, pkg.SPLIT_REDUCE_LAST),
+    modes = [(BULK, 0), (FUSED, 0)] if not split else [(BULK, pkg.SPLIT_REDUCE_LAST), (FUSED, pkg.SPLIT_REDUCE_LAST),
                                            (BULK, pkg.SPLIT_REDUCE_AUTO),
                                            (BULK, pkg.SPLIT_REDUCE_KERNEL)]
     outs = []
